@@ -53,7 +53,7 @@ def _compile(src: str, verbose: bool, force: bool = True) -> str:
     if not force and not _stale(src, obj):
         return obj
     # the device assembly is kept next to the object (-save-temps=obj) for
-    # the SrcC hazard check that follows the build
+    # the hazard check that follows the build
     cmd = [HIPCC] + FLAGS + ["-save-temps=obj", "-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".cpp"):
         cmd = [HIPCC, "-x", "hip"] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
@@ -81,13 +81,13 @@ def build(verbose: bool = False, force: bool = True) -> str:
     return LIB
 
 
-# Kernels whose built code must pass the SrcC hazard check (isa_check.py);
+# Kernels whose built code must pass the hazard check (isa_check.py);
 # the build fails if one of them does not.  Other kernels are reported.
 ENFORCED = ("beamform_",)
 
 
 def check_hazards(verbose: bool = False) -> dict:
-    """Run the SrcC hazard check over the device assembly of this build;
+    """Run the hazard check (SrcC and store data) over the device assembly of this build;
     raise if an enforced kernel fails it.  Returns {kernel: violations}."""
     import glob
     try:
@@ -102,10 +102,10 @@ def check_hazards(verbose: bool = False) -> dict:
     enforced = {k: v for k, v in bad.items() if any(e in k for e in ENFORCED)}
     if verbose or enforced:
         for k, v in bad.items():
-            print(f"hazard check: {k.rsplit(':', 1)[-1][:90]}: {len(v)} SrcC rewrites "
-                  f"within {isa_check.WAIT} wait states", flush=True)
+            print(f"hazard check: {k.rsplit(':', 1)[-1][:90]}: {len(v)} early "
+                  f"rewrites of an MFMA's SrcC or a store's data", flush=True)
     if enforced:
-        raise RuntimeError(f"SrcC hazard check failed for {len(enforced)} enforced kernels")
+        raise RuntimeError(f"hazard check failed for {len(enforced)} enforced kernels")
     return bad
 
 

@@ -1,5 +1,5 @@
-"""Static check of the built gfx950 kernels for one hazard the compiler does
-not cover: an instruction other than an MFMA writing a register that an
+"""Static check of the built gfx950 kernels for two hazards the compiler does
+not cover.  SrcC: an instruction other than an MFMA writing a register that an
 earlier MFMA reads as its accumulator input (SrcC) when that register is not
 the MFMA's own destination, fewer than ``WAIT`` wait states after the MFMA.
 
@@ -22,6 +22,13 @@ destination when its data returns, tens to hundreds of cycles after it
 issues, long after the MFMA issued before it has read SrcC; the corruption
 seen came from a VALU write.
 
+Store data: a VALU or MFMA write of a register that holds the data of a store
+wider than 8 bytes, fewer than ``STORE_WAIT`` wait states after the store.
+The store reads its last register's lanes 12-15 (of each 16) last; a write
+right behind it was observed to reach memory there.  The compiler keeps two
+wait states for global and flat stores and for buffer stores without a scalar
+offset, and none for buffer stores with one.
+
 ``python -m paper_1412_4907_amd.isa_check <file.s>...`` prints the findings
 per kernel and exits non-zero if there are any.
 """
@@ -31,6 +38,7 @@ import re
 import sys
 
 WAIT = 7
+STORE_WAIT = 2
 
 _RANGE = re.compile(r'^([va])\[(\d+):(\d+)\]$')
 _ONE = re.compile(r'^([va])(\d+)$')
@@ -116,10 +124,48 @@ def _scan(insts, labels, start, srcc, budget, seen):
     return None
 
 
+_WIDE_STORE = re.compile(r'^(buffer|global|flat|scratch)_store_(dwordx[34]|b96|b128)')
+
+
+def _store_scan(insts, labels, start, data, budget, seen):
+    """First vector-register write of `data` reachable from instruction
+    `start` within `budget` wait states: (wait states used, index) or None."""
+    i, ws = start, 0
+    while i < len(insts) and ws < budget:
+        op, ops, _ = insts[i]
+        if op == 's_nop':
+            ws += int(ops[0], 0) + 1
+            i += 1
+            continue
+        if op.startswith('v_') and ops and _regs(ops[0]) & data:
+            return ws, i
+        if op.startswith('s_cbranch') or op == 's_branch':
+            tgt = ops[0] if ops else ''
+            if tgt in labels and (tgt, ws) not in seen:
+                seen.add((tgt, ws))
+                hit = _store_scan(insts, labels, labels[tgt], data, budget - ws - 1, seen)
+                if hit is not None:
+                    return ws + 1 + hit[0], hit[1]
+            if op == 's_branch':
+                return None
+        if op in ('s_endpgm', 's_setpc_b64'):
+            return None
+        ws += 1
+        i += 1
+    return None
+
+
 def check_kernel(insts, labels, wait: int = WAIT) -> list:
-    """[(line of the MFMA, line of the write, wait states)] violations."""
+    """[(line of the MFMA or store, line of the write, wait states)]
+    violations."""
     out = []
     for i, (op, ops, ln) in enumerate(insts):
+        if _WIDE_STORE.match(op):
+            data = _regs(ops[0] if op.startswith('buffer') else ops[1])
+            hit = _store_scan(insts, labels, i + 1, data, STORE_WAIT, set())
+            if hit is not None:
+                out.append((ln, insts[hit[1]][2], hit[0]))
+            continue
         if not op.startswith('v_mfma') or len(ops) < 4:
             continue
         srcc, dst = _regs(ops[3]), _regs(ops[0])
@@ -146,8 +192,8 @@ def check_files(paths, wait: int = WAIT) -> dict:
 def main(argv) -> int:
     bad = check_files(argv)
     for k, v in bad.items():
-        print(f"{k}: {len(v)} SrcC rewrites within {WAIT} wait states "
-              f"(first: MFMA line {v[0][0]}, write line {v[0][1]}, {v[0][2]} wait states)")
+        print(f"{k}: {len(v)} early rewrites of an MFMA's SrcC or a store's data "
+              f"(first: line {v[0][0]}, write line {v[0][1]}, {v[0][2]} wait states)")
     return 1 if bad else 0
 
 

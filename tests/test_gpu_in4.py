@@ -178,3 +178,28 @@ def test_4bit_accumulate(gpu):
     ra = oracle.beamform(W, oracle.unpack4(x4a), I)
     rb = oracle.beamform(W, oracle.unpack4(x4b), I)
     assert_parity(got, ra + rb, 1e-5, "4-bit accumulate")
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
+def test_4bit_power_under_load_bitwise(gpu, prec):
+    """Enough units that every CU holds several waves: the pipelined form's
+    stores (scaled data in registers the next beam tile reuses) must give the
+    bits of the streamed tile in every window, on every run."""
+    N, C, B, T, I = 32, 256, 128, 8192, 16
+    print(f"4-bit under load {prec}", flush=True)
+    pos, dirs, freqs, _ = _case((N, C, 4, 16, I), 5)
+    import torch
+    x = torch.randint(0, 256, (C, T, N), dtype=torch.uint8, device=gpu,
+                      generator=torch.Generator(device=gpu).manual_seed(11))
+    dirs = synth.random_dirs(B, np.random.default_rng(6))
+    with bf.Plan(N, C, B, T, I, precision=prec, input_bits=4) as plan:
+        plan.set_weights(pos, dirs, freqs)
+        got = torch.empty(plan.p_shape, device=gpu)
+        ref = torch.empty_like(got)
+        plan.set_tile(4, 8, 2, 0, 1)
+        plan.run(x, ref)
+        plan.set_tile(4, 4, 1, 1, 4) if prec == "fp32" else plan.set_tile(4, 8, 1, 1, 4)
+        for _ in range(3):
+            got.fill_(-1.0)
+            plan.run(x, got)
+            assert torch.equal(got, ref)

@@ -69,6 +69,36 @@ def test_an_mfma_overwriting_srcc_ends_the_window():
 """)
 
 
+def test_write_of_store_data_too_soon_is_flagged():
+    bad = _check(HEAD + """
+    buffer_store_dwordx4 v[98:101], v103, s[8:11], s5 offen nt
+    v_mul_f32_e32 v101, 0x3b800000, v29
+    s_endpgm
+""")
+    (v,) = bad.values()
+    assert v[0][2] == 0
+    bad = _check(HEAD + """
+    global_store_dwordx4 v[4:5], v[98:101], off
+    s_branch .LBB0_1
+.LBB0_1:
+    v_mfma_f32_16x16x32_f16 v[98:101], v[38:41], v[140:143], 0
+    s_endpgm
+""")
+    assert len(bad) == 1
+
+
+def test_store_data_rewritten_late_enough_or_narrow_passes():
+    assert not _check(HEAD + """
+    buffer_store_dwordx4 v[98:101], v103, s[8:11], 0 offen nt
+    v_or_b32_e32 v103, v102, v185
+    s_nop 0
+    v_mul_f32_e32 v101, 0x3b800000, v29
+    buffer_store_dwordx2 v[98:99], v103, s[8:11], s5 offen
+    v_mul_f32_e32 v98, 0x3b800000, v29
+    s_endpgm
+""")
+
+
 def test_built_kernels_pass():
     files = sorted(glob.glob(os.path.join(ROOT, "_build", "*-hip-amdgcn-amd-amdhsa-gfx950.s")))
     if not files:
