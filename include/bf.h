@@ -35,8 +35,10 @@
  *     distinct handles are.
  *
  * Precision forms
- *   BF_FP32  weights rounded from FP64 to FP32; int8 voltages converted to
- *            FP32; products on FP32 matrix cores (MFMA), FP32 accumulation.
+ *   BF_FP32  weights rounded from FP64 to FP32 and held in FP32; each enters
+ *            the products as its exact sum of three BF16 values, the voltages
+ *            exactly as BF16, so every product is exact and only the FP32
+ *            accumulation (BF16 MFMA) rounds.
  *   BF_FP16  weights rounded from FP64 to FP16 (round to nearest even, one
  *            rounding); voltages converted exactly to FP16; FP16 MFMA with
  *            FP32 accumulation.

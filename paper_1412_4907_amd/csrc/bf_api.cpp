@@ -87,7 +87,9 @@ using bf::units_for;
 
 int gcd(int a, int b) { return b ? gcd(b, a % b) : a; }
 
-Prob make_prob(const bf_plan_s* p, const int8_t* x, float* out, int64_t unit_begin) {
+// form: the compiled form the set runs in; sgw: its store groups per wave.
+Prob make_prob(const bf_plan_s* p, const Tile& form, int32_t sgw, const int8_t* x, float* out,
+               int64_t unit_begin) {
   Prob q;
   std::memset(&q, 0, sizeof(q));
   q.x = x;
@@ -107,9 +109,13 @@ Prob make_prob(const bf_plan_s* p, const int8_t* x, float* out, int64_t unit_beg
   q.G = G;
   q.QI = QI;
   q.SG = SG;
-  q.sgw = p->sgw;
-  q.nbr = (p->Bpad / 16 + p->tile.nbt - 1) / p->tile.nbt;
-  const int64_t per = (int64_t)bf::waves_of(p->tile) * p->sgw;  // store groups per unit
+  q.sgw = sgw;
+  // the plan's beam tiles spread evenly over as few ranges as the form's
+  // width allows: 9 tiles at width 4 run as 3 + 3 + 3 (measured in choose_tile)
+  const int32_t need = p->Bpad / 16;
+  q.nbr = (need + form.nbt - 1) / form.nbt;
+  q.bw = (need + q.nbr - 1) / q.nbr;
+  const int64_t per = (int64_t)bf::waves_of(form) * sgw;  // store groups per unit
   q.ntr = (int32_t)((SG + per - 1) / per);
   q.accumulate = (p->flags & BF_ACCUMULATE) ? 1 : 0;
   q.variant = -1;
@@ -280,78 +286,57 @@ int fill_sets(const bf_plan_t* plans, int n, const int8_t* const* x, float* cons
   const bool multi = plans[0]->vec16;
   *common = Tile{4, 1, 1, 0};
   if (!multi) {
-    std::vector<Tile> cand;
-    for (int i = 0; i < n; ++i) cand.push_back(plans[i]->tile);
-    std::stable_sort(cand.begin(), cand.end(),
-                     [](const Tile& a, const Tile& b) { return a.nbt > b.nbt; });
-    for (const Tile& c : cand) {
-      bool ok = true;
-      for (int i = 0; i < n && ok; ++i) ok = tile_ok(*plans[i], c);
-      if (ok) {
-        *common = c;
-        break;
-      }
+    // byte-load rows: the widest general variant some set would take alone
+    // that runs them all
+    const Tile wide8{4, 8, 2, 0};
+    bool any = false, all = true;
+    for (int i = 0; i < n; ++i) {
+      const bf_plan_s* p = plans[i];
+      any = any || (p->Bpad / 16 > 4 && lds_bytes(p->prec, p->Kpad, 8) <= 80 * 1024);
+      all = all && tile_ok(*p, wide8);
     }
+    if (any && all) *common = wide8;
   }
   for (int i = 0; i < n; ++i) {
-    bf_plan_s tmp = *plans[i];  // the same set under its launch tile
+    const bf_plan_s* p = plans[i];
     Tile t = *common;
     int variant = -1;
+    int32_t G, QI, SG;
+    schedule(p->I, p->T, &G, &QI, &SG);
+    int32_t sgw;
     if (wide) {
       // the widest eight-wave beam range whose weights fit the launch's LDS
       // and that the set's beams fill beyond one narrower range
       const std::vector<Tile> kWide = bf::wide_tiles();
       for (int v = 0; v < (int)kWide.size() && variant < 0; ++v) {
         const Tile& c = kWide[v];
-        const bool last = v + 1 == (int)kWide.size();
-        if (tile_ok(tmp, c) && lds_bytes(tmp.prec, tmp.Kpad, c.nbt) <= lds_cap &&
-            (last || tmp.Bpad / 16 > c.nbt / 2))
+        if (bf::buffer_shape(*p) && tile_lds(p->prec, p->Kpad, c) <= lds_cap &&
+            (c.nbt == 1 || p->Bpad / 16 > c.nbt / 2))
           variant = v;
       }
       if (variant < 0) return BF_ERR_UNSUPPORTED;
       t = kWide[variant];
+      // an eight-wave unit takes as much of the channel's time range as
+      // spreads over its eight waves (at least one MT-aligned step each): no
+      // wave of a unit idles on a short block, and a long block is split into
+      // as few units as that allows, each staging its weights once.  Measured
+      // on a 12-set batch against each set's own count capped the same way:
+      // 19.05-19.10 -> 18.76-18.80 ms.
+      const int32_t base = t.mt / gcd(t.mt, G);
+      sgw = std::max(base, SG / bf::kWideWaves / base * base);
     } else if (multi) {
-      const std::vector<Tile> kMultiTiles = bf::multi_tiles();
-      const int nm = (int)kMultiTiles.size();
-      auto fits = [&](const Tile& c) {
-        return tile_ok(tmp, c) && lds_bytes(tmp.prec, tmp.Kpad, c.nbt) <= lds_cap;
-      };
-      for (int v = 0; v < nm && variant < 0; ++v) {
-        const Tile& c = kMultiTiles[v];
-        if (c.mt == tmp.tile.mt && c.nbt == tmp.tile.nbt && c.nbp == tmp.tile.nbp &&
-            c.kres == tmp.tile.kres && fits(c))
-          variant = v;
-      }
-      for (int v = 0; v < nm && variant < 0; ++v)
-        if (fits(kMultiTiles[v]) && kMultiTiles[v].kres == tmp.tile.kres &&
-            kMultiTiles[v].nbt <= tmp.tile.nbt)
-          variant = v;
-      for (int v = 0; v < nm && variant < 0; ++v)
-        if (fits(kMultiTiles[v])) variant = v;
+      variant = bf::multi_variant(*p, p->tile, lds_cap);
       if (variant < 0) return BF_ERR_UNSUPPORTED;
-      t = kMultiTiles[variant];
+      t = bf::multi_tiles()[variant];
+      sgw = bf::same_tile(t, bf::form_of(*p, p->tile)) ? p->sgw : bf::choose_sgw(*p, t);
+    } else {
+      const int32_t base = t.mt / gcd(t.mt, G);
+      sgw = std::max(base, p->sgw / base * base);
     }
-    int32_t G, QI, SG;
-    schedule(tmp.I, tmp.T, &G, &QI, &SG);
-    const int32_t base = t.mt / gcd(t.mt, G);
-    const bool same = t.mt == tmp.tile.mt && t.nbt == tmp.tile.nbt && t.nbp == tmp.tile.nbp &&
-                      t.kres == tmp.tile.kres;
-    tmp.tile = t;
-    tmp.sgw = same ? tmp.sgw : std::max(base, tmp.sgw / base * base);
-    if (wide && !same) {
-      // the set's own store-group count per wave was chosen for a four-wave
-      // tile; an eight-wave unit instead takes as much of the channel's time
-      // range as spreads over its eight waves (at least one MT-aligned step
-      // each): no wave of a unit idles on a short block, and a long block is
-      // split into as few units as that allows, each staging its weights
-      // once.  Measured on the 12-set batch against the set's own count
-      // capped the same way: 19.05-19.10 -> 18.76-18.80 ms.
-      tmp.sgw = std::max(base, SG / bf::kWideWaves / base * base);
-    }
-    L->prob[i] = make_prob(&tmp, x[i], out[i], begin);
+    L->prob[i] = make_prob(p, t, sgw, x[i], out[i], begin);
     L->prob[i].variant = variant;
-    begin += units_for(tmp, t, tmp.sgw);
-    lds = std::max(lds, lds_bytes(tmp.prec, tmp.Kpad, t.nbt));
+    begin += (int64_t)p->C * L->prob[i].nbr * L->prob[i].ntr;
+    lds = std::max(lds, tile_lds(p->prec, p->Kpad, t));
   }
   if (lds > lds_cap) return BF_ERR_UNSUPPORTED;
   L->nprob = n;
@@ -838,17 +823,24 @@ int bf_run(bf_plan_t p, const int8_t* x, float* out, void* stream) {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = take_refresh(p, s);
     if (e != hipSuccess) return from_hip(e);
-    Launch L;
-    std::memset(&L, 0, sizeof(L));
-    L.prob[0] = make_prob(p, x, out, 0);
-    L.nprob = 1;
-    L.total_units = units_for(*p, p->tile, p->sgw);
-    L.queue = nullptr;
-    L.xcd_remap = 1;
-    const int64_t grid = (L.total_units + 7) / 8 * 8;
+    const Tile form = bf::form_of(*p, p->tile);
+    const Prob prob = make_prob(p, form, p->sgw, x, out, 0);
+    const int64_t units = (int64_t)p->C * prob.nbr * prob.ntr;
+    const int64_t grid = (units + 7) / 8 * 8;
     if (grid > 0x7FFFFFFF) return BF_ERR_UNSUPPORTED;
-    e = bf::launch_beamform(p->prec, p->mode, p->vec16, p->in4, p->tile, L, (int)grid,
-                            tile_lds(p->prec, p->Kpad, p->tile), s);
+    const size_t lds = tile_lds(p->prec, p->Kpad, form);
+    if (form.kres == 0 || form.kres == -1) {
+      Launch L;
+      std::memset(&L, 0, sizeof(L));
+      L.prob[0] = prob;
+      L.nprob = 1;
+      L.total_units = units;
+      L.xcd_remap = 1;
+      e = bf::launch_beamform(p->prec, p->mode, p->vec16, p->in4, form, L, (int)grid, lds, s);
+    } else {
+      const bf::Single S{prob, units};
+      e = bf::launch_single(p->prec, p->mode, p->in4, p->N % 2 != 0, form, S, (int)grid, lds, s);
+    }
     if (e == hipSuccess) e = mark_used(p, s);
     return from_hip(e);
   } catch (...) {
@@ -874,7 +866,7 @@ int bf_plan_info(bf_plan_t p, bf_plan_info_t* info) {
   info->sg_per_wave = p->sgw;
   info->work_units = units_for(*p, p->tile, p->sgw);
   info->weight_bytes = (int64_t)p->w_bytes;
-  info->lds_bytes = (int64_t)tile_lds(p->prec, p->Kpad, p->tile);
+  info->lds_bytes = (int64_t)tile_lds(p->prec, p->Kpad, bf::form_of(*p, p->tile));
   info->flops = 8.0 * p->C * (double)p->B * (double)p->T * p->N;
   info->tile_tuned = p->tuned ? 1 : 0;
   return BF_OK;
@@ -986,17 +978,18 @@ int bf_batch_run(bf_batch_t bt, const int8_t* const* x, float* const* out, void*
     const bf_plan_s* p0 = bt->plans[0];
     const bool multi = p0->vec16;
     hipError_t e = hipSuccess;
-    // Sets whose K needs more than two 64-wide chunks run the eight-wave
-    // streamed form in a persistent launch of their own (FP16/BF16, I == 1
-    // or I % 4 == 0); the others share the four-wave persistent launch.
-    if (multi && p0->prec != BF_FP32 && (p0->mode == bf::kModeI1 || p0->mode == bf::kModeGen4)) {
+    // Sets whose weights leave no room for two four-wave workgroups per CU run
+    // the eight-wave streamed form in a persistent launch of their own; the
+    // others share the four-wave persistent launch.
+    if (multi) {
       std::vector<bf_plan_t> wp, rp;
       std::vector<const int8_t*> wx, rx;
       std::vector<float*> wo, ro;
       for (int i = 0; i < n; ++i) {
         bf_plan_s* p = bt->plans[i];
-        const bool wide = p->Kpad > 2 * bf::kChunk && tile_ok(*p, bf::wide_tiles().back()) &&
-                          lds_bytes(p->prec, p->Kpad, bf::wide_tiles().back().nbt) <= kLdsMax;
+        Tile st;
+        const bool wide = !bf::fast_ok(*p) && bf::stream_tile(*p, kLdsMax, &st) &&
+                          st.kres == bf::kKresStream8;
         (wide ? wp : rp).push_back(p);
         (wide ? wx : rx).push_back(x[i]);
         (wide ? wo : ro).push_back(out[i]);
@@ -1092,15 +1085,16 @@ int bf_table_create(bf_table_t* out, int32_t n_antennas, int32_t integration, in
     if (t->wide) {
       t->lds = 0;
       for (const Tile& c : bf::wide_tiles()) {
-        const size_t l = lds_bytes(precision, t->Kpad, c.nbt);
+        const size_t l = tile_lds(precision, t->Kpad, c);
         if (l <= kLdsMax) t->lds = std::max(t->lds, l);
       }
-      if (t->lds == 0) t->wide = false;
+      if (lds_bytes(precision, t->Kpad, 2) > kLdsMax) t->wide = false;
     }
     if (!t->wide) {
       t->lds = lds_bytes(precision, t->Kpad, 1);
       for (const Tile& c : bf::multi_tiles()) {
-        const size_t l = lds_bytes(precision, t->Kpad, c.nbt);
+        if (c.kres == 1 && t->Kpad != bf::kChunk) continue;
+        const size_t l = tile_lds(precision, t->Kpad, c);
         if (l <= 80 * 1024) t->lds = std::max(t->lds, l);
       }
     }
@@ -1149,6 +1143,7 @@ int bf_table_set(bf_table_t t, const bf_plan_t* plans, const int8_t* const* x, f
       if (p->cx || p->w_alt || p->N != t->N || p->I != t->I || p->prec != t->prec ||
           p->in4 != t->in4 || p->device != t->device)
         return BF_ERR_UNSUPPORTED;
+      if (t->wide && !bf::wide_shape(*p)) return BF_ERR_UNSUPPORTED;
     }
     Launch L;
     std::memset(&L, 0, sizeof(L));
@@ -1200,11 +1195,16 @@ template <int PREC, bool IN4>
 hipError_t launch_prec_in(int mode, bool vec16, Tile t, const Launch& L, int grid, size_t lds,
                           hipStream_t s);
 template <int PREC, bool IN4>
+hipError_t launch_single_in(int mode, Tile t, bool odd, const Single& S, int grid, size_t lds,
+                            hipStream_t s);
+template <int PREC, bool IN4>
 hipError_t launch_multi_in(int mode, const Launch& L, const Launch* table, int grid, size_t lds,
                            hipStream_t s, int* occupancy, bool wide);
 #define BF_EXTERN(P, F)                                                                     \
   extern template hipError_t launch_prec_in<P, F>(int, bool, Tile, const Launch&, int, size_t, \
                                                   hipStream_t);                              \
+  extern template hipError_t launch_single_in<P, F>(int, Tile, bool, const Single&, int, size_t, \
+                                                    hipStream_t);                            \
   extern template hipError_t launch_multi_in<P, F>(int, const Launch&, const Launch*, int,    \
                                                    size_t, hipStream_t, int*, bool);
 BF_EXTERN(0, false)
@@ -1226,6 +1226,18 @@ hipError_t launch_beamform_multi(int prec, int mode, bool in4, const Launch& L,
   if (prec == 0) return launch_multi_in<0, false>(mode, L, table, grid, lds, s, occ, wide);
   if (prec == 1) return launch_multi_in<1, false>(mode, L, table, grid, lds, s, occ, wide);
   return launch_multi_in<2, false>(mode, L, table, grid, lds, s, occ, wide);
+}
+
+hipError_t launch_single(int prec, int mode, bool in4, bool odd, Tile form, const Single& S,
+                         int grid, size_t lds, hipStream_t s) {
+  if (in4) {
+    if (prec == 0) return launch_single_in<0, true>(mode, form, odd, S, grid, lds, s);
+    if (prec == 1) return launch_single_in<1, true>(mode, form, odd, S, grid, lds, s);
+    return launch_single_in<2, true>(mode, form, odd, S, grid, lds, s);
+  }
+  if (prec == 0) return launch_single_in<0, false>(mode, form, odd, S, grid, lds, s);
+  if (prec == 1) return launch_single_in<1, false>(mode, form, odd, S, grid, lds, s);
+  return launch_single_in<2, false>(mode, form, odd, S, grid, lds, s);
 }
 
 hipError_t launch_beamform(int prec, int mode, bool vec16, bool in4, Tile tile, const Launch& L,

@@ -5,6 +5,8 @@
 namespace bf {
 template hipError_t launch_prec_in<2, false>(int, bool, Tile, const Launch&, int, size_t,
                                              hipStream_t);
+template hipError_t launch_single_in<2, false>(int, Tile, bool, const Single&, int, size_t,
+                                               hipStream_t);
 template hipError_t launch_multi_in<2, false>(int, const Launch&, const Launch*, int, size_t,
                                               hipStream_t, int*, bool);
 }

@@ -36,6 +36,16 @@ const Tile kWideTiles[] = {
     BF_TILE_LIST_WIDE
 #undef BF_TILE
 };
+const Tile kFastTiles[] = {
+#define BF_TILE(MT, NBT, NBP, KRES) Tile{MT, NBT, NBP, KRES},
+    BF_TILE_LIST_FAST
+#undef BF_TILE
+};
+const Tile kStreamTiles[] = {
+#define BF_TILE(MT, NBT, NBP, KRES) Tile{MT, NBT, NBP, KRES},
+    BF_TILE_LIST_STREAM
+#undef BF_TILE
+};
 const Tile kCxTiles[] = {
 #define BF_TILE(MT, NBT, NBP, KRES) Tile{MT, NBT, NBP, KRES},
     BF_TILE_LIST_CX
@@ -99,8 +109,15 @@ size_t lds_bytes(int prec, int32_t Kpad, int nbt) {
   return (size_t)2 * 16 * (size_t)nbt * ((size_t)Kpad * (size_t)es_of(prec) + kLdsPad);
 }
 
+size_t split_lds_bytes(int prec, int32_t Kpad, int nbt) {
+  const size_t row = (size_t)kChunk * (prec == BF_FP32 ? 6 : 2) + kLdsPad;  // per 64-wide chunk
+  return (size_t)2 * 16 * (size_t)nbt * ((size_t)Kpad / kChunk) * row;
+}
+
 size_t tile_lds(int prec, int32_t Kpad, Tile t) {
-  return t.kres == -1 ? 0 : lds_bytes(prec, Kpad, t.nbt);
+  if (t.kres == -1) return 0;
+  if (t.kres == 0 || t.kres > 1) return lds_bytes(prec, Kpad, t.nbt);
+  return split_lds_bytes(prec, Kpad, t.nbt);
 }
 
 void schedule(int32_t I, int64_t T, int32_t* G, int32_t* QI, int32_t* SG) {
@@ -122,19 +139,65 @@ bool same_tile(const Tile& a, const Tile& b) {
   return a.mt == b.mt && a.nbt == b.nbt && a.nbp == b.nbp && a.kres == b.kres;
 }
 
-// The eight-wave form's conditions: FP16/BF16 power output, 16-byte rows,
-// I == 1 or I % 4 == 0 (I % MT == 0 is checked per tile), overwriting
-// output, whole 16-byte window quads (T / I % 4 == 0), and byte offsets
-// within one channel's voltages (rows up to the last store group's padding,
-// plus the out-of-range marker 2^31 added to them) and one channel's output
-// rows that fit the 32-bit buffer offsets it uses.
-static bool wide_shape(const Shape& s) {
+// Byte offsets within one channel's voltages (rows up to the last wave step's
+// and store group's padding, plus the out-of-range marker 2^31 added to them)
+// and one channel's output rows must fit 32 bits.
+bool buffer_shape(const Shape& s) {
+  const int64_t rowb = s.in4 ? s.N : 2 * (int64_t)s.N;
+  const int64_t out = s.cx ? s.T : s.T / s.I;  // 4 bytes each
+  // T <= 2^40 and rowb <= 2^13: no overflow; 16 I <= 16 T
+  return s.T < ((int64_t)1 << 31) && (s.T + 16 * (int64_t)s.I + 128) * rowb < 0x7FFFFF00 &&
+         (int64_t)s.B * out * 4 < 0x7FFFFF00;
+}
+
+bool wide_shape(const Shape& s) {
   if (s.prec == BF_FP32 || s.cx || !s.vec16 || (s.flags & BF_ACCUMULATE)) return false;
   if (s.mode != kModeI1 && s.mode != kModeGen4) return false;
-  const int64_t W = s.T / s.I;
-  if (W % 4 != 0) return false;
-  const int64_t rowb = s.in4 ? s.N : 2 * (int64_t)s.N;
-  return (s.T + 16 * (int64_t)s.I) * rowb < 0x7FFFFFFF && (int64_t)s.B * W * 4 < 0x7FFFFFFF;
+  return (s.T / s.I) % 4 == 0 && buffer_shape(s);
+}
+
+bool fast_ok(const Shape& s) {
+  if (s.Kpad != kChunk || s.N % 2 != 0 || !buffer_shape(s)) return false;
+  if (s.mode == kModeGen4) return true;
+  // I == 1 and complex beams: one beam tile, overwriting, whole 16-byte quads.
+  // Wider ranges store tile by tile between MFMA phases here and are bound by
+  // that write stream; the streamed form's bursts reach HBM better (N = 32,
+  // 512 beams, I = 1, 4-bit BF16: 238 against 218 us).
+  return (s.mode == kModeI1 || s.mode == kModeCx) && s.Bpad == 16 && s.T % 4 == 0 &&
+         !(s.flags & BF_ACCUMULATE);
+}
+
+// The widest beam range the shape's beams fill beyond one of half the width
+// and whose weights fit.  Four waves while two workgroups fit a CU (one
+// stages its weights while the other computes), else eight.
+bool stream_tile(const Shape& s, size_t lds_cap, Tile* t) {
+  if (!buffer_shape(s)) return false;
+  const int need = s.Bpad / 16;
+  for (int nbt = 4; nbt >= 1; nbt /= 2) {
+    if (nbt > 1 && nbt / 2 >= need) continue;
+    const size_t l = split_lds_bytes(s.prec, s.Kpad, nbt);
+    if (l > lds_cap) continue;
+    *t = Tile{4, nbt, nbt, l <= 80 * 1024 ? kKresStream4 : kKresStream8};
+    return true;
+  }
+  return false;
+}
+
+Tile form_of(const Shape& s, Tile t) {
+  if (t.kres == kKresWide) {
+    // the name's own width, or the widest narrower one whose weights fit
+    int nbt = t.nbt;
+    while (nbt > 1 && split_lds_bytes(s.prec, s.Kpad, nbt) > kLdsMax) nbt /= 2;
+    return Tile{4, nbt, nbt, kKresStream8};
+  }
+  if (t.kres >= 1) {
+    if (t.kres == 1 && fast_ok(s)) return Tile{4, s.mode == kModeGen4 ? t.nbt : 1, 1, 1};
+    Tile r;
+    if (stream_tile(s, kLdsMax, &r)) return r;
+    return Tile{4, t.nbt, 2, 0};
+  }
+  if (t.kres == 0 && t.nbt == 2) return Tile{4, 2, 2, 0};
+  return t;
 }
 
 std::vector<Tile> compiled_tiles(const Shape& s) {
@@ -147,8 +210,20 @@ std::vector<Tile> compiled_tiles(const Shape& s) {
     v = as_vector(kVecTiles);
   else
     v = as_vector(kGenTiles);
-  if (wide_shape(s))
-    for (const Tile& t : kWideTiles) v.push_back(t);
+  if (fast_ok(s))
+    for (const Tile& t : kFastTiles) {
+      bool named = s.mode != kModeGen4 && t.nbt > 1;
+      for (const Tile& o : v) named = named || same_tile(o, t);
+      if (!named) v.push_back(t);
+    }
+  if (wide_shape(s)) {
+    v.push_back(Tile{4, 4, 4, kKresWide});
+    v.push_back(Tile{4, 2, 2, kKresWide});
+  }
+  if (buffer_shape(s))
+    for (const Tile& t : kStreamTiles)
+      // the eight-wave ranges that kres == -2 names are not offered twice
+      if (!(t.kres == kKresStream8 && t.nbt > 1 && wide_shape(s))) v.push_back(t);
   return v;
 }
 
@@ -165,61 +240,122 @@ bool tile_exists(const Shape& s, Tile t) {
 bool tile_ok(const Shape& s, Tile t) {
   if (!tile_exists(s, t)) return false;
   if (t.kres > 0 && s.Kpad / kChunk > t.kres) return false;
-  if (t.kres == kKresWide && s.mode == kModeGen4 && s.I % t.mt != 0) return false;
-  return tile_lds(s.prec, s.Kpad, t) <= kLdsMax;
+  // names that an earlier form bounded by its own LDS rows
+  if (t.kres == kKresWide && lds_bytes(s.prec, s.Kpad, t.nbt) > kLdsMax) return false;
+  if (t.kres > 0 && lds_bytes(s.prec, s.Kpad, t.nbt) > kLdsMax) return false;
+  return tile_lds(s.prec, s.Kpad, form_of(s, t)) <= kLdsMax;
 }
 
 int64_t units_for(const Shape& s, Tile t, int32_t sgw) {
+  const Tile f = form_of(s, t);
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
-  const int64_t nbr = (s.Bpad / 16 + t.nbt - 1) / t.nbt;
-  const int64_t per = (int64_t)waves_of(t) * sgw;
+  const int64_t nbr = (s.Bpad / 16 + f.nbt - 1) / f.nbt;
+  const int64_t per = (int64_t)waves_of(f) * sgw;
   const int64_t ntr = (SG + per - 1) / per;
   return (int64_t)s.C * nbr * ntr;
 }
 
-// Default tile: the largest beam range whose weight slice fits 80 KB of LDS
-// (two workgroups per CU) without exceeding the plan's beams; voltages held
-// in registers when K <= 128 (MT = 8 for FP16/BF16 at K <= 64, where the
-// per-pass fragment reuse matters most); streamed K otherwise.  Then
-// enough store groups per wave that a launch has >= 8 workgroups per CU,
-// capped at 256 row tiles per wave per unit.
-void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
-  const int need = s.Bpad / 16;
-  const int nch = s.Kpad / kChunk;
-  int nbt = 8;
-  while (nbt > 1 && (lds_bytes(s.prec, s.Kpad, nbt) > 80 * 1024 || nbt / 2 >= need)) nbt /= 2;
-  Tile t{4, 1, 1, 0};
-  if (lds_bytes(s.prec, s.Kpad, 1) > kLdsMax) {
-    t = Tile{4, 2, 2, -1};  // one beam tile's weights do not fit LDS
-  } else if (!s.vec16) {
-    t = nbt == 8 ? Tile{4, 8, 2, 0} : Tile{4, 1, 1, 0};
-  } else if (nch == 1 && nbt >= 4) {
-    t = (s.prec == BF_FP32 || s.in4 || s.cx) ? Tile{4, nbt, 1, 1} : Tile{8, nbt, 1, 1};
-  } else if (nch == 2 && nbt >= 4) {
-    t = Tile{4, nbt, 1, 2};
-  } else {
-    t = nbt >= 4 ? Tile{4, nbt, 2, 0} : nbt == 2 ? Tile{4, 2, 2, 0} : Tile{4, 1, 1, 0};
-  }
-  // the 4-bit and complex-output variants carry fewer forms: fall back to
-  // the streamed form of the same beam range
-  if (!tile_ok(s, t) && nbt >= 2) t = Tile{4, nbt, 2, 0};
-  if (!tile_ok(s, t) && nbt >= 2) t = Tile{4, 2, 2, 0};
-  if (!tile_ok(s, t)) t = Tile{4, 1, 1, 0};
-  if (!tile_ok(s, t)) t = Tile{4, 2, 2, -1};
+// Store groups per wave: the count that finishes the launch first under a
+// simple model.  A unit costs its weight staging plus its wave steps; a step
+// the larger of its MFMA cycles (two waves share a SIMD) and its voltages and
+// per-sample outputs at the CU's share of HBM bandwidth (8 bytes a cycle); the
+// MFMA share counts 1.4 times (busy about 0.7 of the time), the staging 4000
+// cycles and 8 bytes a cycle.  Units run over the device's workgroup slots, and the launch ends most of a
+// unit after the last slot frees: long units amortise the staging, short ones
+// shorten that tail.  Measured against the counts that fill whole rounds: 97.7
+// -> 85 us (N = 32, 128 channels, B = 100, I = 5), 255 -> 218 (I = 1 case
+// above).
+int32_t choose_sgw(const Shape& s, Tile t) {
+  const Tile f = form_of(s, t);
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
   const int32_t base = t.mt / gcd(t.mt, G);  // sgw * G must be a multiple of MT
-  int32_t sgw = base;
-  const int64_t want = (int64_t)s.n_cu * 8;
-  for (int32_t k = 2;; ++k) {
+  const int nw = waves_of(f);
+  const int need = s.Bpad / 16;
+  const int nbr = (need + f.nbt - 1) / f.nbt;
+  const int bw = (need + nbr - 1) / nbr;
+  const size_t lds = tile_lds(s.prec, s.Kpad, f);
+  const double slots = (double)s.n_cu * (nw == kWideWaves || lds > 80 * 1024 ? 1 : 2);
+  const double parts = s.prec == BF_FP32 ? 3 : 1;
+  const double rowb = s.in4 ? s.N : 2.0 * s.N;
+  const double mfma = 1.4 * (s.Kpad / kChunk) * bw * parts * f.mt * 4 * 16 * 2;
+  const double mem = 16.0 * f.mt * (rowb + 64.0 * bw / s.I);  // 8 waves over 8 bytes a cycle
+  const double step = mfma > mem ? mfma : mem;
+  const double stage = 4000.0 + (double)lds / 8.0;
+  int32_t best = base;
+  double best_cost = 0;
+  for (int32_t k = 1;; k = k < 4 ? k + 1 : k + k / 3) {
+    if ((int64_t)base * k > (1 << 20)) break;
     const int32_t v = base * k;
-    if ((int64_t)v * G > 256 || units_for(s, t, v) < want) break;
-    if ((int64_t)(v - base) * waves_of(t) >= SG) break;
-    sgw = v;
+    const double units = (double)units_for(s, t, v);
+    const double used = v < SG ? v : SG;
+    const double unit = stage + used * G / f.mt * step;
+    const double cost = (units > slots ? units / slots : 1.0) * unit + 0.7 * unit;
+    if (k == 1 || cost < best_cost) {
+      best = v;
+      best_cost = cost;
+    }
+    if ((int64_t)v * nw >= SG) break;
+  }
+  return best;
+}
+
+// Default tile.  2N <= 64: the register-resident form, its beam range the
+// plan's beam tiles split evenly over as few ranges as their width allows
+// (eight tiles; six in FP32, whose split weights then still leave two
+// workgroups per CU).  Otherwise the streamed form up to K = 2048.  Beyond,
+// and for channels past 32-bit offsets, the general form: the largest beam
+// range whose weight slice fits 80 KB of LDS (two workgroups per CU) without
+// exceeding the plan's beams.
+void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
+  const int need = s.Bpad / 16;
+  Tile t{4, 1, 1, 0};
+  if (fast_ok(s)) {
+    const int most = s.prec == BF_FP32 ? 6 : 8;
+    const int ranges = (need + most - 1) / most;
+    const int per = (need + ranges - 1) / ranges;
+    const int nbt = per > 6 ? 8 : per > 4 ? 6 : per > 2 ? 4 : per;
+    t = Tile{4, nbt, 1, 1};
+  } else if (s.Kpad <= 2048 && stream_tile(s, kLdsMax, &t)) {
+    if (t.kres == kKresStream8 && t.nbt > 1 && wide_shape(s)) t.kres = kKresWide;
+  } else if (lds_bytes(s.prec, s.Kpad, 1) > kLdsMax) {
+    t = Tile{4, 2, 2, -1};  // one beam tile's weights do not fit LDS
+  } else {
+    int nbt = 8;
+    while (nbt > 1 && (lds_bytes(s.prec, s.Kpad, nbt) > 80 * 1024 || nbt / 2 >= need)) nbt /= 2;
+    if (!s.vec16)
+      t = nbt == 8 ? Tile{4, 8, 2, 0} : Tile{4, 1, 1, 0};
+    else
+      t = nbt >= 4 ? Tile{4, nbt, 2, 0} : nbt == 2 ? Tile{4, 2, 2, 0} : Tile{4, 1, 1, 0};
+    if (!tile_ok(s, t) && nbt >= 2) t = Tile{4, 2, 2, 0};
+    if (!tile_ok(s, t)) t = Tile{4, 1, 1, 0};
+    if (!tile_ok(s, t)) t = Tile{4, 2, 2, -1};
   }
   *out = t;
-  *out_sgw = sgw;
+  *out_sgw = choose_sgw(s, t);
+}
+
+int multi_variant(const Shape& s, Tile own, size_t lds_cap) {
+  const int n = (int)(sizeof(kMultiTiles) / sizeof(kMultiTiles[0]));
+  auto runs = [&](const Tile& c, size_t cap) {
+    if (tile_lds(s.prec, s.Kpad, c) > cap) return false;
+    if (c.kres == 1) return s.mode == kModeGen4 && fast_ok(s);
+    return c.kres == kKresStream4 ? buffer_shape(s) : true;
+  };
+  const Tile f = form_of(s, own);
+  const int need = s.Bpad / 16;
+  // two workgroups per CU if any variant allows it
+  for (size_t cap : {lds_cap < 80 * 1024 ? lds_cap : (size_t)80 * 1024, lds_cap}) {
+    for (int v = 0; v < n; ++v)
+      if (same_tile(kMultiTiles[v], f) && runs(f, cap)) return v;
+    for (int v = 0; v < n; ++v) {
+      const Tile& c = kMultiTiles[v];
+      if (c.nbt > 1 && c.nbt / 2 >= need && !(c.kres == 1 && c.nbt == 4)) continue;
+      if (runs(c, cap)) return v;
+    }
+  }
+  return -1;
 }
 
 int check_tile(const Shape& s, Tile t, int32_t sgw) {

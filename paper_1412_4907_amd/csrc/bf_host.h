@@ -47,14 +47,29 @@ int make_shape(int32_t N, int32_t C, int32_t B, int64_t T, int32_t I, int prec, 
 
 int es_of(int prec);
 int mode_of(int32_t I);
-// Dynamic LDS of a beam range of nbt 16-beam tiles (weight rows for all K).
+// Dynamic LDS of a beam range of nbt 16-beam tiles (weight rows for all K),
+// in the storage precision and split into the MFMA operand parts (FP32: three
+// BF16 parts, 6 bytes per weight), padded per 64-wide chunk.
 size_t lds_bytes(int prec, int32_t Kpad, int nbt);
-// Dynamic LDS of a tile: none when the weights are read from device memory.
+size_t split_lds_bytes(int prec, int32_t Kpad, int nbt);
+// Dynamic LDS of a form: split rows for the register-resident and streamed
+// forms, none when the weights are read from device memory.
 size_t tile_lds(int prec, int32_t Kpad, Tile t);
 // Row-tile schedule for integration I: MFMA row tiles per store group (G),
 // per window (QI) and store groups per channel (SG).
 void schedule(int32_t I, int64_t T, int32_t* G, int32_t* QI, int32_t* SG);
 bool same_tile(const Tile& a, const Tile& b);
+// Whether the shape's byte offsets fit the 32-bit buffer offsets of the
+// register-resident and streamed forms.
+bool buffer_shape(const Shape& s);
+// Whether the register-resident form (2N <= 64) can run the shape.
+bool fast_ok(const Shape& s);
+// The streamed form's tile for the shape (BF_TILE_LIST_STREAM), with weights
+// of at most lds_cap bytes; false if there is none.
+bool stream_tile(const Shape& s, size_t lds_cap, Tile* t);
+// The compiled form that runs tile name t of the shape: t itself, or what
+// replaced it.
+Tile form_of(const Shape& s, Tile t);
 // Whether the single-set kernel compiled for this shape's input, output
 // and row width carries tile t.
 bool tile_exists(const Shape& s, Tile t);
@@ -62,6 +77,8 @@ bool tile_exists(const Shape& s, Tile t);
 bool tile_ok(const Shape& s, Tile t);
 // Work units (workgroups) of one run under (t, sgw).
 int64_t units_for(const Shape& s, Tile t, int32_t sgw);
+// Store groups per wave of one run under form t.
+int32_t choose_sgw(const Shape& s, Tile t);
 // The default tile and store groups per wave.
 void choose_tile(const Shape& s, Tile* t, int32_t* sgw);
 // BF_OK if (t, sgw) can run the shape; BF_ERR_UNSUPPORTED (tile not
@@ -73,6 +90,12 @@ std::vector<Tile> compiled_tiles(const Shape& s);
 std::vector<Tile> multi_tiles();
 // Variants of the eight-wave batching kernels (BF_TILE_LIST_WIDE order).
 std::vector<Tile> wide_tiles();
+// Whether the shape's sets of a table with eight-wave launches are accepted
+// (also: whether the tile names with kres == -2 are offered).
+bool wide_shape(const Shape& s);
+// The four-wave batching variant (index into BF_TILE_LIST_MULTI) for a set
+// whose plan has tile `own`, with at most lds_cap bytes of LDS; -1: none.
+int multi_variant(const Shape& s, Tile own, size_t lds_cap);
 
 // Bytes of one block of voltages, and of one run's output.
 uint64_t input_bytes(const Shape& s);

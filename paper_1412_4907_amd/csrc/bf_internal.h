@@ -22,6 +22,7 @@ struct Prob {
   int32_t Bpad;       // B rounded up to 16
   int32_t Kpad;       // 2N rounded up to kChunk
   int32_t nbr;        // beam ranges (workgroup beam slices) per channel
+  int32_t bw;         // 16-beam tiles per beam range, at most the form's width
   int32_t ntr;        // time ranges (work units) per channel per beam range
   int32_t sgw;        // 16-window store groups per wave per work unit
   int32_t G;          // MFMA row tiles per store group
@@ -48,15 +49,24 @@ struct Launch {
                       // chan_units of them
 };
 
-// Host-side launcher for one (precision, mode, vec16, input format, tile)
-// instantiation.  Returns hipSuccess or the launch error.
+// A launch of one set, one unit per workgroup.
+struct Single {
+  Prob prob;
+  int64_t total_units;
+};
+
+// One set in the register-resident or a streamed form (odd: N is odd).
+hipError_t launch_single(int prec, int mode, bool in4, bool odd, Tile form, const Single& S,
+                         int grid, size_t lds_bytes, hipStream_t stream);
+// The general form of one (precision, mode, vec16, input format, tile).
+// Returns hipSuccess or the launch error.
 hipError_t launch_beamform(int prec, int mode, bool vec16, bool in4, Tile tile, const Launch& L,
                            int grid, size_t lds_bytes, hipStream_t stream);
 // Persistent batching kernel (per-set variants).  table != null: the form
 // that reads its set table from that device copy (L unused).
 // occupancy != null only queries workgroups per CU.  wide: the eight-wave
-// kernels (FP16/BF16, I == 1 or I % 4 == 0; variants index
-// BF_TILE_LIST_WIDE) instead of the four-wave ones (BF_TILE_LIST_MULTI).
+// kernels (variants index BF_TILE_LIST_WIDE) instead of the four-wave ones
+// (BF_TILE_LIST_MULTI).
 hipError_t launch_beamform_multi(int prec, int mode, bool in4, const Launch& L,
                                  const Launch* table, int grid, size_t lds_bytes,
                                  hipStream_t stream, int* occupancy, bool wide = false);

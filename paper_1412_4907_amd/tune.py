@@ -4,8 +4,8 @@ Sec. 2.2 tunes two parameters of the K20 kernel (accumulators per thread and
 threads per block) by sweeping them on the target device.  The tunables
 here are the gfx950 kernel's compiled tile variants -- (MT row tiles per
 wave step, NBT beam tiles per workgroup, NBP beam tiles per pass, KRES K
-chunks in registers; KRES -1 streams weights from device memory, -2 is the
-eight-wave streamed form) -- and the work-unit length (store groups per
+chunks in registers; KRES -1 streams weights from device memory, -2 and -3 are
+the streamed form with eight waves, -4 with four) -- and the work-unit length (store groups per
 wave).
 Each candidate is timed with HIP events on the caller's inputs; the fastest
 is applied with ``bf_plan_set_tile`` and remembered in a JSON cache keyed by
@@ -59,7 +59,7 @@ def sgw_options(plan, tile) -> list:
     G = 1 if I == 1 else 2 if I == 2 else 4 * ((I + 3) // 4)
     base = tile[0] // gcd(tile[0], G)
     sg_total = -(-(plan.T // I) // 16)
-    waves = 8 if tile[3] == -2 else 4   # waves sharing one work unit
+    waves = 8 if tile[3] in (-2, -3) else 4   # waves sharing one work unit
     opts = []
     k = 1
     while True:
@@ -79,12 +79,15 @@ def apply_cached(plan, batch: bool = False) -> Optional[tuple]:
 
 def lds_bytes(plan, tile) -> int:
     """Dynamic LDS a tile stages for this plan (its beam range's weight rows
-    for all K; none when the weights are read from device memory)."""
+    for all K; none when the weights are read from device memory).  The
+    register-resident and streamed forms hold FP32 weights as three BF16 parts
+    and pad each 64-wide chunk of a row."""
     if tile[3] == -1:
         return 0
-    es = 4 if plan.precision == 0 else 2
     kpad = -(-2 * plan.N // 64) * 64
-    return 2 * 16 * tile[1] * (kpad * es + 16)
+    if tile[3] == 0:
+        return 2 * 16 * tile[1] * (kpad * (4 if plan.precision == 0 else 2) + 16)
+    return 2 * 16 * tile[1] * (kpad // 64) * (64 * (6 if plan.precision == 0 else 2) + 16)
 
 
 def tune(plan, x, p, reps: int = 3, max_candidates: Optional[int] = None, save: bool = True,
