@@ -27,6 +27,7 @@ struct bf_plan_s : bf::Shape {
   Tile tile{4, 1, 1, 0};
   int32_t sgw = 1;
   bool tuned = false;  // tile taken from the tile cache
+  bool asked = false;  // tile set by the caller or taken from the tile cache
   int device = 0;
   size_t w_bytes = 0;
   void* w_dev = nullptr;  // the weights runs read
@@ -283,6 +284,7 @@ int fill_sets(const bf_plan_t* plans, int n, const int8_t* const* x, float* cons
     }
   int64_t begin = 0;
   size_t lds = 0;
+  double cycles[bf::kMaxProbs];
   const bool multi = plans[0]->vec16;
   *common = Tile{4, 1, 1, 0};
   if (!multi) {
@@ -325,7 +327,7 @@ int fill_sets(const bf_plan_t* plans, int n, const int8_t* const* x, float* cons
       const int32_t base = t.mt / gcd(t.mt, G);
       sgw = std::max(base, SG / bf::kWideWaves / base * base);
     } else if (multi) {
-      variant = bf::multi_variant(*p, p->tile, lds_cap);
+      variant = bf::multi_variant(*p, p->asked ? &p->tile : nullptr, lds_cap);
       if (variant < 0) return BF_ERR_UNSUPPORTED;
       t = bf::multi_tiles()[variant];
       sgw = bf::same_tile(t, bf::form_of(*p, p->tile)) ? p->sgw : bf::choose_sgw(*p, t);
@@ -335,8 +337,18 @@ int fill_sets(const bf_plan_t* plans, int n, const int8_t* const* x, float* cons
     }
     L->prob[i] = make_prob(p, t, sgw, x[i], out[i], begin);
     L->prob[i].variant = variant;
-    begin += (int64_t)p->C * L->prob[i].nbr * L->prob[i].ntr;
+    cycles[i] = bf::unit_cycles(*p, t, sgw, 2);
     lds = std::max(lds, tile_lds(p->prec, p->Kpad, t));
+  }
+  // longest units first, so that the launch does not end on one
+  for (int i = 1; i < n; ++i)
+    for (int j = i; j > 0 && cycles[j] > cycles[j - 1]; --j) {
+      std::swap(cycles[j], cycles[j - 1]);
+      std::swap(L->prob[j], L->prob[j - 1]);
+    }
+  for (int i = 0; i < n; ++i) {
+    L->prob[i].unit_begin = begin;
+    begin += (int64_t)L->prob[i].C * L->prob[i].nbr * L->prob[i].ntr;
   }
   if (lds > lds_cap) return BF_ERR_UNSUPPORTED;
   L->nprob = n;
@@ -462,7 +474,7 @@ bool apply_tuned(bf_plan_s* p, bool batch) {
     if (bf::check_tile(*p, it->tile, it->sgw) != BF_OK) return false;
     p->tile = it->tile;
     p->sgw = it->sgw;
-    p->tuned = true;
+    p->tuned = p->asked = true;
     return true;
   }
   return false;
@@ -881,6 +893,7 @@ int bf_plan_set_tile(bf_plan_t p, int32_t mt, int32_t nbt, int32_t nbp, int32_t 
   p->tile = t;
   p->sgw = sgw;
   p->tuned = false;
+  p->asked = true;
   return BF_OK;
 }
 
@@ -978,18 +991,26 @@ int bf_batch_run(bf_batch_t bt, const int8_t* const* x, float* const* out, void*
     const bf_plan_s* p0 = bt->plans[0];
     const bool multi = p0->vec16;
     hipError_t e = hipSuccess;
-    // Sets whose weights leave no room for two four-wave workgroups per CU run
-    // the eight-wave streamed form in a persistent launch of their own; the
-    // others share the four-wave persistent launch.
-    if (multi) {
+    // Sets whose own tile is the streamed form with eight waves run it in a
+    // persistent launch of their own, the others in the four-wave one, where
+    // each launch fills the device by itself; otherwise every set joins the
+    // four-wave launch (two launches run one after the other: 110 against 308 us
+    // for four sets of 10 to 112 channels).
+    int64_t wide_units = 0, four_units = 0;
+    for (int i = 0; i < n && multi; ++i) {
+      const bf_plan_s* p = bt->plans[i];
+      const bool w = bf::form_of(*p, p->tile).kres == bf::kKresStream8;
+      (w ? wide_units : four_units) += units_for(*p, p->tile, p->sgw);
+    }
+    const bool split = wide_units > 0 && wide_units >= 2 * (int64_t)p0->n_cu &&
+                       (four_units == 0 || four_units >= 4 * (int64_t)p0->n_cu);
+    if (multi && split) {
       std::vector<bf_plan_t> wp, rp;
       std::vector<const int8_t*> wx, rx;
       std::vector<float*> wo, ro;
       for (int i = 0; i < n; ++i) {
         bf_plan_s* p = bt->plans[i];
-        Tile st;
-        const bool wide = !bf::fast_ok(*p) && bf::stream_tile(*p, kLdsMax, &st) &&
-                          st.kres == bf::kKresStream8;
+        const bool wide = bf::form_of(*p, p->tile).kres == bf::kKresStream8;
         (wide ? wp : rp).push_back(p);
         (wide ? wx : rx).push_back(x[i]);
         (wide ? wo : ro).push_back(out[i]);

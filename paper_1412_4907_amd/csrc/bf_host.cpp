@@ -145,8 +145,9 @@ bool same_tile(const Tile& a, const Tile& b) {
 bool buffer_shape(const Shape& s) {
   const int64_t rowb = s.in4 ? s.N : 2 * (int64_t)s.N;
   const int64_t out = s.cx ? s.T : s.T / s.I;  // 4 bytes each
-  // T <= 2^40 and rowb <= 2^13: no overflow; 16 I <= 16 T
-  return s.T < ((int64_t)1 << 31) && (s.T + 16 * (int64_t)s.I + 128) * rowb < 0x7FFFFF00 &&
+  // I % 4 != 0: a step can reach into the store group behind the last one
+  const int64_t pad = (s.mode == kModeGen ? 32 : 16) * (int64_t)s.I + 128;
+  return s.T < ((int64_t)1 << 31) && (s.T + pad) * rowb < 0x7FFFFF00 &&
          (int64_t)s.B * out * 4 < 0x7FFFFF00;
 }
 
@@ -256,70 +257,130 @@ int64_t units_for(const Shape& s, Tile t, int32_t sgw) {
   return (int64_t)s.C * nbr * ntr;
 }
 
-// Store groups per wave: the count that finishes the launch first under a
-// simple model.  A unit costs its weight staging plus its wave steps; a step
-// the larger of its MFMA cycles (two waves share a SIMD) and its voltages and
-// per-sample outputs at the CU's share of HBM bandwidth (8 bytes a cycle); the
-// MFMA share counts 1.4 times (busy about 0.7 of the time), the staging 4000
-// cycles and 8 bytes a cycle.  Units run over the device's workgroup slots, and the launch ends most of a
-// unit after the last slot frees: long units amortise the staging, short ones
-// shorten that tail.  Measured against the counts that fill whole rounds: 97.7
-// -> 85 us (N = 32, 128 channels, B = 100, I = 5), 255 -> 218 (I = 1 case
-// above).
-int32_t choose_sgw(const Shape& s, Tile t) {
-  const Tile f = form_of(s, t);
+// Cycles of one unit of form f with v store groups per wave where wg of its
+// workgroups share a CU, from a simple model: its weight staging (8000 cycles
+// and 8 bytes a cycle) plus its wave steps.  A step costs the larger of two:
+// its MFMA and VALU cycles (conversion per chunk, detection per beam tile),
+// shared by the waves that are resident on the SIMD (one alone overlaps
+// nothing: 1.4 times); and its HBM bytes at the CU's share of the bandwidth (8
+// bytes a cycle; the voltages are fetched once for all beam ranges of a
+// channel).
+double unit_cycles(const Shape& s, Tile f, int32_t v, int wg) {
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
-  const int32_t base = t.mt / gcd(t.mt, G);  // sgw * G must be a multiple of MT
   const int nw = waves_of(f);
   const int need = s.Bpad / 16;
   const int nbr = (need + f.nbt - 1) / f.nbt;
-  const int bw = (need + nbr - 1) / nbr;
-  const size_t lds = tile_lds(s.prec, s.Kpad, f);
-  const double slots = (double)s.n_cu * (nw == kWideWaves || lds > 80 * 1024 ? 1 : 2);
+  // the register-resident form computes every tile of its width
+  const int bw = f.kres == 1 ? f.nbt : (need + nbr - 1) / nbr;
+  const double groups = (double)(SG + v - 1) / v;  // waves with work in a channel's range
+  const double waves = (double)wg * (groups < nw ? groups : nw);
+  const double per_simd = waves > 5.6 ? waves / 4 : 1.4;
   const double parts = s.prec == BF_FP32 ? 3 : 1;
+  const double halves = (2 * s.N + 31) / 32;
   const double rowb = s.in4 ? s.N : 2.0 * s.N;
-  const double mfma = 1.4 * (s.Kpad / kChunk) * bw * parts * f.mt * 4 * 16 * 2;
-  const double mem = 16.0 * f.mt * (rowb + 64.0 * bw / s.I);  // 8 waves over 8 bytes a cycle
-  const double step = mfma > mem ? mfma : mem;
-  const double stage = 4000.0 + (double)lds / 8.0;
+  const double mfma = halves * bw * parts * f.mt * 2 * 16;
+  const double valu = 1.6 * (halves * 40 * 4 + bw * 32.0 * f.mt);
+  const double mem = waves * 16 * f.mt * (rowb / nbr + 64.0 * bw / s.I) / 8;
+  const double work = (mfma + valu) * per_simd;
+  const double step = work > mem ? work : mem;
+  const double steps = s.mode == kModeGen ? s.I / 4.0 : (double)G / f.mt;  // per store group
+  return 8000.0 + (double)tile_lds(s.prec, s.Kpad, f) / 8.0 + (v < SG ? v : SG) * steps * step;
+}
+
+// Cycles of one launch: units run over the device's workgroup slots in whole
+// rounds, or, over many rounds, until a quarter of a unit after the last slot
+// frees.  Eight waves cost 5% more at a tie.
+static double form_cycles(const Shape& s, const Tile& f, int32_t v) {
+  int32_t G, QI, SG;
+  schedule(s.I, s.T, &G, &QI, &SG);
+  const int nw = waves_of(f);
+  const int nbr = (s.Bpad / 16 + f.nbt - 1) / f.nbt;
+  const size_t lds = tile_lds(s.prec, s.Kpad, f);
+  // workgroups per CU by registers, then LDS
+  int wg = nw == kWideWaves ? (f.nbt == 1 ? 2 : 1)
+           : f.nbt == 1     ? 4
+           : f.nbt == 2 && f.kres != 1 ? 3 : 2;
+  while (wg > 1 && lds * wg > kLdsMax) --wg;
+  const double units =
+      (double)s.C * nbr * (double)((SG + (int64_t)nw * v - 1) / ((int64_t)nw * v));
+  if (units < (double)s.n_cu * wg) wg = (int)std::ceil(units / s.n_cu);
+  const double rounds = units / ((double)s.n_cu * wg);
+  const double whole = std::ceil(rounds), tail = rounds + 0.25;
+  return (whole > tail ? whole : tail) * unit_cycles(s, f, v, wg) *
+         (nw == kWideWaves ? 1.05 : 1.0);
+}
+
+// The store groups per wave that finish first under form_cycles; *cycles: their
+// cost.  Long units amortise the staging, short ones fill the device.  Against
+// the counts that fill whole rounds: N = 32, 128 channels, B = 100, I = 5: 97.7
+// -> 85 us.  Per-sample outputs (I == 1, complex) are bound by the write stream,
+// which reaches HBM better in short runs: at most 16 groups, 4 for one beam tile
+// (N = 32, 512 beams, I = 1: 218 us at 16, 222 at 32, 245 at 8; 16 complex
+// beams: 762 at 4, 786 at 8, 816 at 32).
+static int32_t best_sgw(const Shape& s, const Tile& f, int32_t base, double* cycles) {
+  int32_t G, QI, SG;
+  schedule(s.I, s.T, &G, &QI, &SG);
+  const int32_t most = s.I > 1 ? 1 << 20 : f.nbt == 1 ? 4 : 16;
   int32_t best = base;
-  double best_cost = 0;
   for (int32_t k = 1;; k = k < 4 ? k + 1 : k + k / 3) {
-    if ((int64_t)base * k > (1 << 20)) break;
+    if ((int64_t)base * k > most) break;
     const int32_t v = base * k;
-    const double units = (double)units_for(s, t, v);
-    const double used = v < SG ? v : SG;
-    const double unit = stage + used * G / f.mt * step;
-    const double cost = (units > slots ? units / slots : 1.0) * unit + 0.7 * unit;
-    if (k == 1 || cost < best_cost) {
+    const double c = form_cycles(s, f, v);
+    if (k == 1 || c < *cycles) {
       best = v;
-      best_cost = cost;
+      *cycles = c;
     }
-    if ((int64_t)v * nw >= SG) break;
+    if ((int64_t)v * waves_of(f) >= SG) break;
   }
   return best;
 }
 
-// Default tile.  2N <= 64: the register-resident form, its beam range the
-// plan's beam tiles split evenly over as few ranges as their width allows
-// (eight tiles; six in FP32, whose split weights then still leave two
-// workgroups per CU).  Otherwise the streamed form up to K = 2048.  Beyond,
-// and for channels past 32-bit offsets, the general form: the largest beam
-// range whose weight slice fits 80 KB of LDS (two workgroups per CU) without
-// exceeding the plan's beams.
+// sgw * (row tiles per store group) must be a multiple of MT
+static int32_t base_sgw(const Shape& s, const Tile& t) {
+  int32_t G, QI, SG;
+  schedule(s.I, s.T, &G, &QI, &SG);
+  return t.mt / gcd(t.mt, G);
+}
+
+int32_t choose_sgw(const Shape& s, Tile t) {
+  double cycles = 0;
+  return best_sgw(s, form_of(s, t), base_sgw(s, t), &cycles);
+}
+
+// Default tile: the register-resident form (2N <= 64) or the streamed form (up
+// to K = 2048) of the width and wave count that finish first under
+// form_cycles.  Beyond, and for channels past 32-bit offsets, the general
+// form: the largest beam range whose weight slice fits 80 KB of LDS (two
+// workgroups per CU) without exceeding the plan's beams.
 void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
   const int need = s.Bpad / 16;
-  Tile t{4, 1, 1, 0};
+  double least = 0;
+  bool found = false;
+  auto consider = [&](const Tile& t, const Tile& f) {
+    if (tile_lds(s.prec, s.Kpad, f) > kLdsMax) return;
+    if (f.nbt > 1 && f.kres != 1 && f.nbt / 2 >= need) return;
+    double c = 0;
+    const int32_t v = best_sgw(s, f, base_sgw(s, t), &c);
+    if (found && c >= least) return;
+    found = true;
+    least = c;
+    *out = t;
+    *out_sgw = v;
+  };
   if (fast_ok(s)) {
-    const int most = s.prec == BF_FP32 ? 6 : 8;
-    const int ranges = (need + most - 1) / most;
-    const int per = (need + ranges - 1) / ranges;
-    const int nbt = per > 6 ? 8 : per > 4 ? 6 : per > 2 ? 4 : per;
-    t = Tile{4, nbt, 1, 1};
-  } else if (s.Kpad <= 2048 && stream_tile(s, kLdsMax, &t)) {
-    if (t.kres == kKresStream8 && t.nbt > 1 && wide_shape(s)) t.kres = kKresWide;
-  } else if (lds_bytes(s.prec, s.Kpad, 1) > kLdsMax) {
+    for (const Tile& t : kFastTiles)
+      if (s.mode == kModeGen4 || t.nbt == 1) consider(t, t);
+  } else if (buffer_shape(s) && s.Kpad <= 2048) {
+    for (const Tile& f : kStreamTiles) {
+      Tile t = f;
+      if (f.kres == kKresStream8 && f.nbt > 1 && wide_shape(s)) t.kres = kKresWide;
+      if (tile_ok(s, t)) consider(t, f);
+    }
+  }
+  if (found) return;
+  Tile t{4, 1, 1, 0};
+  if (lds_bytes(s.prec, s.Kpad, 1) > kLdsMax) {
     t = Tile{4, 2, 2, -1};  // one beam tile's weights do not fit LDS
   } else {
     int nbt = 8;
@@ -336,14 +397,14 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
   *out_sgw = choose_sgw(s, t);
 }
 
-int multi_variant(const Shape& s, Tile own, size_t lds_cap) {
+int multi_variant(const Shape& s, const Tile* own, size_t lds_cap) {
   const int n = (int)(sizeof(kMultiTiles) / sizeof(kMultiTiles[0]));
   auto runs = [&](const Tile& c, size_t cap) {
     if (tile_lds(s.prec, s.Kpad, c) > cap) return false;
     if (c.kres == 1) return s.mode == kModeGen4 && fast_ok(s);
     return c.kres == kKresStream4 ? buffer_shape(s) : true;
   };
-  const Tile f = form_of(s, own);
+  const Tile f = own ? form_of(s, *own) : Tile{0, 0, 0, 0};
   const int need = s.Bpad / 16;
   // two workgroups per CU if any variant allows it
   for (size_t cap : {lds_cap < 80 * 1024 ? lds_cap : (size_t)80 * 1024, lds_cap}) {
@@ -351,7 +412,7 @@ int multi_variant(const Shape& s, Tile own, size_t lds_cap) {
       if (same_tile(kMultiTiles[v], f) && runs(f, cap)) return v;
     for (int v = 0; v < n; ++v) {
       const Tile& c = kMultiTiles[v];
-      if (c.nbt > 1 && c.nbt / 2 >= need && !(c.kres == 1 && c.nbt == 4)) continue;
+      if (c.nbt > 1 && c.nbt / 2 >= need) continue;  // half its width would do
       if (runs(c, cap)) return v;
     }
   }

@@ -93,9 +93,13 @@ std::vector<Tile> wide_tiles();
 // Whether the shape's sets of a table with eight-wave launches are accepted
 // (also: whether the tile names with kres == -2 are offered).
 bool wide_shape(const Shape& s);
-// The four-wave batching variant (index into BF_TILE_LIST_MULTI) for a set
-// whose plan has tile `own`, with at most lds_cap bytes of LDS; -1: none.
-int multi_variant(const Shape& s, Tile own, size_t lds_cap);
+// The four-wave batching variant (index into BF_TILE_LIST_MULTI) for a set,
+// with at most lds_cap bytes of LDS: the tile `own` if the kernel carries its
+// form (null: none asked for), else the widest beam range the set's beams fill
+// that leaves two workgroups per CU; -1: none.
+int multi_variant(const Shape& s, const Tile* own, size_t lds_cap);
+// Modelled cycles of one unit of form f with v store groups per wave.
+double unit_cycles(const Shape& s, Tile f, int32_t v, int wg);
 
 // Bytes of one block of voltages, and of one run's output.
 uint64_t input_bytes(const Shape& s);
