@@ -348,10 +348,10 @@ int bf_plan_destroy(bf_plan_t plan);
  * device whose workgroups take work units from device queues spanning all
  * sets (one queue counter per XCD; a workgroup drains its own XCD's queue,
  * which holds the channels c with c % 8 == XCD index, then helps the
- * others).  In an FP16/BF16 batch with I == 1 or I % 4 == 0, the sets whose
- * 2N exceeds 128 run in a second persistent launch of the eight-wave
- * streamed form, queued first on the same stream (one launch per kernel
- * form); when all of those sets read one voltage block, its queues hand out
+ * others).  Sets whose own tile is the eight-wave streamed form run in a
+ * second persistent launch of that form, queued first on the same stream,
+ * where they and the other sets each fill the device (else one launch takes
+ * them all); when all of those sets read one voltage block, its queues hand out
  * their units channel by channel over the sets.  All
  * plans must share precision, input format and integration class (I == 1,
  * I == 2, or I >= 3) and have their weights set; up to 16 plans.  The batch
@@ -370,8 +370,9 @@ int bf_batch_tile_candidates(bf_plan_t plan, int32_t* tiles, int32_t max_tiles);
 /* x_dev[i], p_dev[i]: host arrays of device pointers, one per plan, same
  * layout and alignment rules as bf_run; no output may overlap any set's
  * voltages or another set's output (else BF_ERR_INVALID_ARG).  One launch per
- * kernel form on `stream`, each after a one-thread queue reset kernel.  Each set's output is
- * bitwise identical to bf_run of that plan alone. */
+ * kernel form on `stream`; runs of one batch must not overlap (they share its
+ * queue counters, which each launch leaves cleared for the next).  Each set's
+ * output is bitwise identical to bf_run of that plan alone. */
 int bf_batch_run(bf_batch_t batch, const int8_t* const* x_dev, float* const* p_dev, void* stream);
 
 /* Free the batch (not its plans) after its own last bf_batch_run has
@@ -384,8 +385,8 @@ int bf_batch_destroy(bf_batch_t batch);
  * plans changes between blocks; Sec. 2.2 and Sec. 3.2 describe beamforming
  * block after block while new pointings are prepared).  The same persistent
  * kernel as bf_batch_run, but its set table lives in device memory owned by
- * the table, so every bf_table_run enqueues the same two launches with the
- * same arguments: a hipGraph captured around one bf_table_run serves every
+ * the table, so every bf_table_run enqueues the same launch with the same
+ * arguments: a hipGraph captured around one bf_table_run serves every
  * table stored afterwards.
  *
  * bf_table_create: for plans with n_antennas antennas, integration I, the
@@ -418,10 +419,10 @@ int bf_table_create(bf_table_t* out, int32_t n_antennas, int32_t integration, in
 int bf_table_set(bf_table_t table, const bf_plan_t* plans, const int8_t* const* x_dev,
                  float* const* p_dev, int32_t n, void* stream);
 
-/* Enqueues the batched launch over the stored table on `stream` (queue reset
- * kernel + persistent kernel; no allocation, no memset, no host sync), so it
- * may be captured into a hipGraph.  Runs on one stream must not overlap: they
- * share the table and the queue counter. */
+/* Enqueues the batched launch over the stored table on `stream` (one
+ * persistent kernel; no allocation, no memset, no host sync), so it may be
+ * captured into a hipGraph.  Runs must not overlap: they share the table and
+ * the queue counters, which each launch leaves cleared for the next. */
 int bf_table_run(bf_table_t table, void* stream);
 
 /* Free the table after its own last bf_table_set and bf_table_run have

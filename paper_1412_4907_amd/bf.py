@@ -399,7 +399,7 @@ class Batch:
 class Table:
     """Persistent batched launch over a set table kept in device memory
     (``bf_table_create``): ``set`` stores which plans run on which buffers,
-    ``run`` enqueues the same two launches every time, so a graph captured
+    ``run`` enqueues the same launch every time, so a graph captured
     around one ``run`` serves every later ``set``."""
 
     def __init__(self, n_antennas: int, integration: int, precision="fp16", input_bits: int = 8):

@@ -197,6 +197,16 @@ hipError_t dev_alloc(int dev, void** ptr, size_t n) {
   return e;
 }
 
+// Queue counters of n persistent launches, cleared.
+hipError_t queue_alloc(int dev, int n, int32_t** q) {
+  hipError_t e = dev_alloc(dev, (void**)q, (size_t)n * bf::kQueueInts * sizeof(int32_t));
+  DevMem* d = nullptr;
+  if (e == hipSuccess) e = dev_mem(dev, &d);
+  if (e == hipSuccess) e = bf::launch_queue_clear(*q, n * bf::kQueueInts, d->alloc);
+  if (e == hipSuccess) e = hipStreamSynchronize(d->alloc);
+  return e;
+}
+
 // Releases device buffers of `dev` once every event in `after` has
 // completed (events never recorded count as complete); does not wait.
 hipError_t dev_release(int dev, std::initializer_list<hipEvent_t> after,
@@ -957,7 +967,7 @@ int bf_batch_create(bf_batch_t* out, const bf_plan_t* plans, int32_t n) {
     bt->plans.assign(plans, plans + n);
     bt->device = plans[0]->device;
     // queue counters of the two persistent launches (four- and eight-wave)
-    hipError_t e = dev_alloc(bt->device, (void**)&bt->queue, 2 * bf::kQueueInts * sizeof(int32_t));
+    hipError_t e = queue_alloc(bt->device, 2, &bt->queue);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&bt->last_use, hipEventDisableTiming);
     if (e != hipSuccess) {
       (void)dev_release(bt->device, {}, {bt->queue});
@@ -1027,9 +1037,7 @@ int bf_batch_run(bf_batch_t bt, const int8_t* const* x, float* const* out, void*
                                       true);
         if (e != hipSuccess) return from_hip(e);
         int64_t gw = std::min<int64_t>(LW.total_units, (int64_t)p0->n_cu * std::max(1, occ));
-        e = bf::launch_queue_reset(LW.queue, s);
-        if (e == hipSuccess)
-          e = bf::launch_beamform_multi(p0->prec, p0->mode, p0->in4, LW, nullptr,
+        e = bf::launch_beamform_multi(p0->prec, p0->mode, p0->in4, LW, nullptr,
                                         (int)std::max<int64_t>(1, gw), ldw, s, nullptr, true);
         if (e != hipSuccess) return from_hip(e);
         if (!rp.empty()) {
@@ -1051,15 +1059,11 @@ int bf_batch_run(bf_batch_t bt, const int8_t* const* x, float* const* out, void*
     }
     int64_t grid = std::min<int64_t>(L.total_units, (int64_t)p0->n_cu * per_cu);
     if (grid < 1) grid = 1;
-    if (L.total_units > 0) {
-      e = bf::launch_queue_reset(bt->queue, s);
-      if (e == hipSuccess) {
-        e = multi ? bf::launch_beamform_multi(p0->prec, p0->mode, p0->in4, L, nullptr, (int)grid,
-                                              lds, s, nullptr)
-                  : bf::launch_beamform(p0->prec, p0->mode, p0->vec16, p0->in4, common, L,
-                                        (int)grid, lds, s);
-      }
-    }
+    if (L.total_units > 0)
+      e = multi ? bf::launch_beamform_multi(p0->prec, p0->mode, p0->in4, L, nullptr, (int)grid, lds,
+                                            s, nullptr)
+                : bf::launch_beamform(p0->prec, p0->mode, p0->vec16, p0->in4, common, L, (int)grid,
+                                      lds, s);
     for (int i = 0; i < n && e == hipSuccess; ++i) e = mark_used(bt->plans[i], s);
     if (e == hipSuccess) e = hipEventRecord(bt->last_use, s);
     return from_hip(e);
@@ -1127,7 +1131,7 @@ int bf_table_create(bf_table_t* out, int32_t n_antennas, int32_t integration, in
     if (e == hipSuccess) e = hipDeviceGetAttribute(&t->n_cu, hipDeviceAttributeMultiprocessorCount,
                                                    t->device);
     if (e == hipSuccess)
-      e = dev_alloc(t->device, (void**)&t->queue, bf::kQueueInts * sizeof(int32_t));
+      e = queue_alloc(t->device, 1, &t->queue);
     if (e == hipSuccess) e = dev_alloc(t->device, (void**)&t->table, sizeof(Launch));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&t->last_use, hipEventDisableTiming);
     int occ = 0;
@@ -1189,10 +1193,8 @@ int bf_table_run(bf_table_t t, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   Launch unused;
   std::memset(&unused, 0, sizeof(unused));
-  hipError_t e = bf::launch_queue_reset(t->queue, s);
-  if (e == hipSuccess)
-    e = bf::launch_beamform_multi(t->prec, t->mode, t->in4, unused, t->table, t->grid, t->lds, s,
-                                  nullptr, t->wide);
+  hipError_t e = bf::launch_beamform_multi(t->prec, t->mode, t->in4, unused, t->table, t->grid,
+                                           t->lds, s, nullptr, t->wide);
   if (e == hipSuccess) e = record_unless_capturing(t->last_use, s);
   return from_hip(e);
 }

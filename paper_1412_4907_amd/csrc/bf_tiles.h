@@ -18,7 +18,8 @@ constexpr int kKresStream8 = -3;  // streamed form, eight waves
 constexpr int kKresStream4 = -4;  // streamed form, four waves
 constexpr int kXcds = 8;        // accelerator dies (XCDs), each with its own L2
 constexpr int kQueueStride = 16;  // int32 slots between the per-XCD queue counters
-constexpr int kQueueInts = kXcds * kQueueStride;  // one persistent launch's counters
+// one persistent launch's counters: a queue per XCD, and the workgroups done
+constexpr int kQueueInts = (kXcds + 1) * kQueueStride;
 constexpr int kChunk = 64;      // real K elements (32 antennas) per chunk
 constexpr int kLdsPad = 16;     // bytes added to each LDS weight row
 

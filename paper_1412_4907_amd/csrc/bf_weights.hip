@@ -149,8 +149,8 @@ __global__ void __launch_bounds__(64) weights_raw_kernel(const double* __restric
   }
 }
 
-__global__ void queue_reset_kernel(int32_t* q) {
-  if (threadIdx.x < kXcds) q[threadIdx.x * kQueueStride] = 0;
+__global__ void queue_clear_kernel(int32_t* q, int n) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) q[i] = 0;
 }
 
 // Copies a set table from the kernel arguments into device memory, one dword
@@ -195,8 +195,8 @@ hipError_t launch_weights_raw(int prec, const double* wraw, int N, int C, int B,
   return launch(weights_raw_kernel<2>, grid, 64, s, wraw, N, C, B, Bpad, Kpad, w);
 }
 
-hipError_t launch_queue_reset(int32_t* q, hipStream_t s) {
-  return launch(queue_reset_kernel, 1, kXcds, s, q);
+hipError_t launch_queue_clear(int32_t* q, int n, hipStream_t s) {
+  return launch(queue_clear_kernel, 1, 64, s, q, n);
 }
 
 hipError_t launch_table_store(const Launch& L, Launch* dst, hipStream_t s) {

@@ -20,8 +20,8 @@ builds those ideas on one MI355X:
   at admission) and one output buffer per ring slot (block k writes buffer
   k mod slots, so a block's output stays intact while the later blocks that
   can be in flight run); integration state never leaves HBM;
-* the per-block work -- one queue-reset kernel and one persistent beamform
-  launch over every active request -- reads its set table (which requests,
+* the per-block work -- one persistent beamform launch over every active
+  request -- reads its set table (which requests,
   which ring slot, which output buffers) from device memory, so it is
   captured once as a hipGraph and replayed for every block; before each
   replay a one-workgroup kernel stores that block's table;
