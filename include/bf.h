@@ -288,8 +288,7 @@ typedef struct {
   int32_t tile_mt;        /* 16-sample MFMA row tiles per wave step             */
   int32_t tile_nbt;       /* 16-beam tiles per workgroup                        */
   int32_t tile_nbp;       /* 16-beam tiles per accumulator pass                 */
-  int32_t tile_kres;      /* 64-element K chunks held in registers (0: streamed,
-                             -1: streamed, weights read from device memory) */
+  int32_t tile_kres;      /* kernel form, see bf_plan_set_tile                  */
   int32_t sg_per_wave;    /* 16-window store groups per wave per work unit      */
   int64_t work_units;     /* workgroups of one bf_run                           */
   int64_t weight_bytes;   /* device bytes of the weight buffer                  */
@@ -302,10 +301,13 @@ int bf_plan_info(bf_plan_t plan, bf_plan_info_t* info);
 /*
  * Override the plan's tile choice (used by the autotuner): mt row tiles of
  * 16 samples per wave step, nbt 16-beam tiles per workgroup, nbp beam tiles
- * per accumulator pass, kres K chunks of 64 held in registers (0 = streamed
- * K with the unit's weights in LDS, -1 = streamed K with the weights read
- * from device memory), sg_per_wave 16-window store groups per wave per work
- * unit.  A
+ * per accumulator pass, kres the kernel form, sg_per_wave 16-window store
+ * groups per wave per work unit.  kres: 1 or more = voltages and accumulators
+ * in registers, one beam tile at a time (2N <= 64); -4 and -3 (also -2) =
+ * streamed K with four and eight waves per work unit; 0 and -1 = the general
+ * form with the unit's weights in LDS and in device memory.  A tile whose form
+ * does not take the plan (rows, integration, offsets past 2 GiB, LDS) runs the
+ * next form that does.  A
  * combination the library does not compile, or that the plan's K or LDS
  * budget excludes, returns BF_ERR_UNSUPPORTED and leaves the plan unchanged;
  * sg_per_wave * (row tiles per store group) must be a multiple of mt
