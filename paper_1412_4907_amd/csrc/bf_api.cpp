@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -136,18 +137,27 @@ thread_local char g_last_error[256] = "no error";
 // device.  An allocation is made on a private stream that carries nothing
 // else (so waiting for it waits for nothing but the allocation), and a
 // handle's buffers are released with hipFreeAsync on a second private
-// stream, after waits on the handle's own events: destroying a handle never
-// waits for, or is ordered behind, other work on the device.  The pool does
-// not let an allocation wait for a pending release (no internal
-// dependencies): memory is reused only once its release has run.
+// stream once the handle's own events have completed: destroying a handle never
+// waits for, or is ordered behind, other work on the device.  Buffers whose
+// events are still pending are kept aside until a later call finds them
+// completed.  The pool itself is never given a buffer that queued work still
+// reads: released behind a wait for that work, such a buffer was handed to the
+// next handle at once, whose weights the queued run then read.
+// Buffers of a destroyed handle, and the events that end their last use.
+struct Pending {
+  std::vector<hipEvent_t> after;
+  std::vector<void*> ptrs;
+};
 struct DevMem {
   hipStream_t alloc = nullptr;
   hipStream_t release = nullptr;
   hipMemPool_t pool = nullptr;
+  std::vector<Pending> pending;  // guarded by g_mem_mu
 };
 constexpr int kMaxDevices = 64;
 std::mutex g_mem_mu;
 DevMem g_mem[kMaxDevices];
+std::atomic<int> g_pending{0};  // entries of all devices' lists
 
 hipError_t dev_mem(int dev, DevMem** out) {
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
@@ -182,9 +192,44 @@ hipError_t dev_mem(int dev, DevMem** out) {
   return hipSuccess;
 }
 
+// Queries and releases below are no part of a graph that this thread may be
+// capturing.
+struct OutsideCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Releases the buffers of p if all its events have completed (an event never
+// recorded counts as completed).  Under g_mem_mu.
+bool release_done(DevMem* d, const Pending& p) {
+  for (hipEvent_t ev : p.after)
+    if (hipEventQuery(ev) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+  for (hipEvent_t ev : p.after) (void)hipEventDestroy(ev);
+  for (void* ptr : p.ptrs) (void)hipFreeAsync(ptr, d->release);
+  return true;
+}
+
+// Releases what destroyed handles left and has completed since.
+void release_pending() {
+  if (g_pending.load(std::memory_order_relaxed) == 0) return;
+  std::lock_guard<std::mutex> lock(g_mem_mu);
+  OutsideCapture outside;
+  for (DevMem& d : g_mem)
+    for (size_t i = d.pending.size(); i-- > 0;)
+      if (release_done(&d, d.pending[i])) {
+        d.pending.erase(d.pending.begin() + (std::ptrdiff_t)i);
+        --g_pending;
+      }
+}
+
 // n bytes of device memory on `dev`, usable from any stream on return.
 hipError_t dev_alloc(int dev, void** ptr, size_t n) {
   *ptr = nullptr;
+  release_pending();
   DevMem* d = nullptr;
   hipError_t e = dev_mem(dev, &d);
   if (e != hipSuccess) return e;
@@ -207,18 +252,34 @@ hipError_t queue_alloc(int dev, int n, int32_t** q) {
   return e;
 }
 
-// Releases device buffers of `dev` once every event in `after` has
-// completed (events never recorded count as complete); does not wait.
-hipError_t dev_release(int dev, std::initializer_list<hipEvent_t> after,
-                       std::initializer_list<void*> ptrs) {
+// Takes over device buffers of `dev` and the events behind their last use:
+// releases both once every event has completed; does not wait.
+void dev_release(int dev, std::initializer_list<hipEvent_t> after,
+                 std::initializer_list<void*> ptrs) {
+  release_pending();
   DevMem* d = nullptr;
-  hipError_t e = dev_mem(dev, &d);
-  if (e != hipSuccess) return e;
-  for (hipEvent_t ev : after)
-    if (ev && e == hipSuccess) e = hipStreamWaitEvent(d->release, ev, 0);
-  for (void* ptr : ptrs)
-    if (ptr && e == hipSuccess) e = hipFreeAsync(ptr, d->release);
-  return e;
+  if (dev_mem(dev, &d) != hipSuccess) return;
+  std::lock_guard<std::mutex> lock(g_mem_mu);
+  OutsideCapture outside;
+  try {
+    Pending p;
+    for (hipEvent_t ev : after)
+      if (ev) p.after.push_back(ev);
+    for (void* ptr : ptrs)
+      if (ptr) p.ptrs.push_back(ptr);
+    d->pending.reserve(d->pending.size() + 1);
+    if (release_done(d, p)) return;
+    d->pending.push_back(std::move(p));
+    ++g_pending;
+  } catch (...) {  // no host memory for the list
+    for (hipEvent_t ev : after)
+      if (ev) {
+        (void)hipEventSynchronize(ev);
+        (void)hipEventDestroy(ev);
+      }
+    for (void* ptr : ptrs)
+      if (ptr) (void)hipFreeAsync(ptr, d->release);
+  }
 }
 
 // Pinned host staging buffers are recycled rather than freed (hipHostFree
@@ -602,18 +663,16 @@ int bf_plan_destroy(bf_plan_t p) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     (void)hipSetDevice(p->device);
-    // device buffers: released on the device after the plan's own work
-    // (weight generation, refreshes, the runs that read either buffer)
-    (void)dev_release(p->device, {p->geo_done, p->w_ready, p->used_cur, p->used_alt},
-                      {p->w_dev, p->w_alt, p->geo_dev});
     // the pinned staging area is reused by later plans once the copy that
     // read it (ordered before geo_done) is done
     if (p->geo_host) {
       if (p->geo_done) (void)hipEventSynchronize(p->geo_done);
       pinned_release(p->geo_host, p->geo_count * sizeof(double));
     }
-    for (hipEvent_t ev : {p->geo_done, p->w_ready, p->used_cur, p->used_alt})
-      if (ev) (void)hipEventDestroy(ev);
+    // device buffers: released after the plan's own work (weight generation,
+    // refreshes, the runs that read either buffer)
+    dev_release(p->device, {p->geo_done, p->w_ready, p->used_cur, p->used_alt},
+                {p->w_dev, p->w_alt, p->geo_dev});
     (void)hipSetDevice(dev);
     delete p;
     return BF_OK;
@@ -842,6 +901,7 @@ int bf_run(bf_plan_t p, const int8_t* x, float* out, void* stream) {
     if (bf::ranges_overlap(x, bf::input_bytes(*p), out, bf::output_bytes(*p)))
       return BF_ERR_INVALID_ARG;
     if (!p->weights_set && !p->refresh_pending) return BF_ERR_STATE;
+    release_pending();
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = take_refresh(p, s);
     if (e != hipSuccess) return from_hip(e);
@@ -970,7 +1030,7 @@ int bf_batch_create(bf_batch_t* out, const bf_plan_t* plans, int32_t n) {
     hipError_t e = queue_alloc(bt->device, 2, &bt->queue);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&bt->last_use, hipEventDisableTiming);
     if (e != hipSuccess) {
-      (void)dev_release(bt->device, {}, {bt->queue});
+      dev_release(bt->device, {}, {bt->queue});
       delete bt;
       return from_hip(e);
     }
@@ -984,6 +1044,7 @@ int bf_batch_create(bf_batch_t* out, const bf_plan_t* plans, int32_t n) {
 int bf_batch_run(bf_batch_t bt, const int8_t* const* x, float* const* out, void* stream) {
   try {
     if (!bt || !x || !out) return BF_ERR_INVALID_ARG;
+    release_pending();
     const int n = (int)bt->plans.size();
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     for (int i = 0; i < n; ++i) {
@@ -1074,10 +1135,8 @@ int bf_batch_run(bf_batch_t bt, const int8_t* const* x, float* const* out, void*
 
 int bf_batch_destroy(bf_batch_t bt) {
   if (!bt) return BF_OK;
-  // the queue counters are released on the device after the batch's own
-  // last launch
-  (void)dev_release(bt->device, {bt->last_use}, {bt->queue});
-  if (bt->last_use) (void)hipEventDestroy(bt->last_use);
+  // the queue counters are released after the batch's own last launch
+  dev_release(bt->device, {bt->last_use}, {bt->queue});
   delete bt;
   return BF_OK;
 }
@@ -1142,8 +1201,7 @@ int bf_table_create(bf_table_t* out, int32_t n_antennas, int32_t integration, in
                                     &occ, t->wide);
     }
     if (e != hipSuccess) {
-      if (t->last_use) (void)hipEventDestroy(t->last_use);
-      (void)dev_release(t->device, {}, {t->queue, t->table});
+      dev_release(t->device, {t->last_use}, {t->queue, t->table});
       delete t;
       return from_hip(e);
     }
@@ -1190,6 +1248,7 @@ int bf_table_set(bf_table_t t, const bf_plan_t* plans, const int8_t* const* x, f
 
 int bf_table_run(bf_table_t t, void* stream) {
   if (!t) return BF_ERR_INVALID_ARG;
+  release_pending();
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   Launch unused;
   std::memset(&unused, 0, sizeof(unused));
@@ -1201,11 +1260,9 @@ int bf_table_run(bf_table_t t, void* stream) {
 
 int bf_table_destroy(bf_table_t t) {
   if (!t) return BF_OK;
-  // released on the device after the table's own last store and uncaptured
-  // run (launches replayed from a captured graph are the caller's to wait
-  // for)
-  (void)dev_release(t->device, {t->last_use}, {t->queue, t->table});
-  if (t->last_use) (void)hipEventDestroy(t->last_use);
+  // released after the table's own last store and uncaptured run (launches
+  // replayed from a captured graph are the caller's to wait for)
+  dev_release(t->device, {t->last_use}, {t->queue, t->table});
   delete t;
   return BF_OK;
 }
