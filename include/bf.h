@@ -372,9 +372,12 @@ int bf_batch_tile_candidates(bf_plan_t plan, int32_t* tiles, int32_t max_tiles);
 /* x_dev[i], p_dev[i]: host arrays of device pointers, one per plan, same
  * layout and alignment rules as bf_run; no output may overlap any set's
  * voltages or another set's output (else BF_ERR_INVALID_ARG).  One launch per
- * kernel form on `stream`; runs of one batch must not overlap (they share its
- * queue counters, which each launch leaves cleared for the next).  Each set's
- * output is bitwise identical to bf_run of that plan alone. */
+ * kernel form on `stream`.  Runs of one batch share its queue counters, which
+ * each launch leaves cleared for the next, so a run waits on the device for the
+ * batch's last one, whatever its stream.  Replays of a graph that a run was
+ * captured into are the caller's to keep from overlapping other runs; from that
+ * capture on, every run clears the counters in a kernel of its own first.  Each
+ * set's output is bitwise identical to bf_run of that plan alone. */
 int bf_batch_run(bf_batch_t batch, const int8_t* const* x_dev, float* const* p_dev, void* stream);
 
 /* Free the batch (not its plans) after its own last bf_batch_run has
@@ -387,7 +390,7 @@ int bf_batch_destroy(bf_batch_t batch);
  * plans changes between blocks; Sec. 2.2 and Sec. 3.2 describe beamforming
  * block after block while new pointings are prepared).  The same persistent
  * kernel as bf_batch_run, but its set table lives in device memory owned by
- * the table, so every bf_table_run enqueues the same launch with the same
+ * the table, so every bf_table_run enqueues that launch with the same
  * arguments: a hipGraph captured around one bf_table_run serves every
  * table stored afterwards.
  *
@@ -422,9 +425,10 @@ int bf_table_set(bf_table_t table, const bf_plan_t* plans, const int8_t* const* 
                  float* const* p_dev, int32_t n, void* stream);
 
 /* Enqueues the batched launch over the stored table on `stream` (one
- * persistent kernel; no allocation, no memset, no host sync), so it may be
- * captured into a hipGraph.  Runs must not overlap: they share the table and
- * the queue counters, which each launch leaves cleared for the next. */
+ * persistent kernel, behind one that clears the queue counters where
+ * bf_batch_run has one; no allocation, no memset, no host sync), so it may be
+ * captured into a hipGraph.  Runs on several streams follow each other as those
+ * of a batch do; a table must not be stored over while a run reads it. */
 int bf_table_run(bf_table_t table, void* stream);
 
 /* Free the table after its own last bf_table_set and bf_table_run have

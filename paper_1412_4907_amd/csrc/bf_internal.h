@@ -40,7 +40,7 @@ struct Launch {
   Prob prob[kMaxProbs];
   int64_t total_units;
   int32_t* queue;     // persistent mode: kXcds + 1 device counters, kQueueStride
-                      // apart (zero before and after each launch); else null
+                      // apart (zero where a launch starts and where it ends); else null
   int32_t nprob;
   int32_t xcd_remap;  // non-persistent mode: group consecutive units per XCD
   int32_t chan_units; // > 0: every set reads the same voltages (same block,
@@ -88,8 +88,9 @@ hipError_t launch_weights_geom(int prec, const double* pos, const double* dir,
                                int Bpad, int Kpad, void* w, hipStream_t stream);
 hipError_t launch_weights_raw(int prec, const double* wraw, int N, int C, int B, int Bpad,
                               int Kpad, void* w, hipStream_t stream);
-// Clears n queue counters (once, when a batch or table is made: every launch
-// leaves them cleared).
+// Clears n queue counters (before a batch's or table's first launch, and before
+// every one once a launch has been captured; otherwise each launch leaves them
+// cleared).
 hipError_t launch_queue_clear(int32_t* q, int n, hipStream_t stream);
 // Stores a set table into device memory (one workgroup, vector stores), in
 // stream order before the table kernel that reads it.
