@@ -382,16 +382,19 @@ int fill_sets(const bf_plan_t* plans, int n, const int8_t* const* x, float* cons
   const bool multi = plans[0]->vec16;
   *common = Tile{4, 1, 1, 0};
   if (!multi) {
-    // byte-load rows: the widest general variant some set would take alone
-    // that runs them all
-    const Tile wide8{4, 8, 2, 0};
+    // byte-load rows: the widest general variant that some set would take alone
+    // and that runs them all (16 bits: four beam tiles in one pass, so a row's
+    // bytes are loaded and converted once for 64 beams)
+    const bool f32 = plans[0]->prec == BF_FP32;
+    const Tile widest = f32 ? Tile{4, 8, 2, 0} : Tile{4, 4, 4, 0};
     bool any = false, all = true;
     for (int i = 0; i < n; ++i) {
       const bf_plan_s* p = plans[i];
-      any = any || (p->Bpad / 16 > 4 && lds_bytes(p->prec, p->Kpad, 8) <= 80 * 1024);
-      all = all && tile_ok(*p, wide8);
+      any = any || (p->Bpad / 16 > (f32 ? 4 : 1) &&
+                    lds_bytes(p->prec, p->Kpad, widest.nbt) <= 80 * 1024);
+      all = all && tile_ok(*p, widest);
     }
-    if (any && all) *common = wide8;
+    if (any && all) *common = widest;
   }
   for (int i = 0; i < n; ++i) {
     const bf_plan_s* p = plans[i];

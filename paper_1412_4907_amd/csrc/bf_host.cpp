@@ -195,10 +195,14 @@ Tile form_of(const Shape& s, Tile t) {
     if (t.kres == 1 && fast_ok(s)) return Tile{4, s.mode == kModeGen4 ? t.nbt : 1, 1, 1};
     Tile r;
     if (stream_tile(s, kLdsMax, &r)) return r;
-    return Tile{4, t.nbt, 2, 0};
+    t.kres = 0;
   }
-  if (t.kres == 0 && t.nbt == 2) return Tile{4, 2, 2, 0};
-  return t;
+  if (t.kres != 0) return t;
+  // general form: in 16 bits every beam tile of the range in one pass, at most
+  // four; in FP32 two per pass (byte-load rows have no width of four there)
+  if (t.nbt <= 2) return Tile{4, t.nbt, t.nbt, 0};
+  if (s.prec != BF_FP32) return Tile{4, 4, 4, 0};
+  return Tile{4, t.nbt == 8 || !s.vec16 ? 8 : 4, 2, 0};
 }
 
 std::vector<Tile> compiled_tiles(const Shape& s) {
@@ -383,15 +387,14 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
   if (lds_bytes(s.prec, s.Kpad, 1) > kLdsMax) {
     t = Tile{4, 2, 2, -1};  // one beam tile's weights do not fit LDS
   } else {
-    int nbt = 8;
+    int nbt = s.prec == BF_FP32 ? 8 : 4;
     while (nbt > 1 && (lds_bytes(s.prec, s.Kpad, nbt) > 80 * 1024 || nbt / 2 >= need)) nbt /= 2;
-    if (!s.vec16)
-      t = nbt == 8 ? Tile{4, 8, 2, 0} : Tile{4, 1, 1, 0};
-    else
-      t = nbt >= 4 ? Tile{4, nbt, 2, 0} : nbt == 2 ? Tile{4, 2, 2, 0} : Tile{4, 1, 1, 0};
-    if (!tile_ok(s, t) && nbt >= 2) t = Tile{4, 2, 2, 0};
-    if (!tile_ok(s, t)) t = Tile{4, 1, 1, 0};
-    if (!tile_ok(s, t)) t = Tile{4, 2, 2, -1};
+    if (!s.vec16) {
+      // the byte-load rows' wide form, if the beams fill more than one tile
+      const int wide = s.prec == BF_FP32 ? 8 : 4, least = s.prec == BF_FP32 ? 4 : 1;
+      nbt = need > least && lds_bytes(s.prec, s.Kpad, wide) <= 80 * 1024 ? wide : 1;
+    }
+    t = nbt == 8 ? Tile{4, 8, 2, 0} : Tile{4, nbt, nbt, 0};
   }
   *out = t;
   *out_sgw = choose_sgw(s, t);

@@ -53,22 +53,27 @@ constexpr int waves_of(Tile t) {
   BF_TILE(8, 8, 1, 1) BF_TILE(4, 8, 2, 1) BF_TILE(4, 8, 1, 1) BF_TILE(8, 4, 1, 1)  \
   BF_TILE(4, 4, 1, 1) BF_TILE(4, 8, 1, 2) BF_TILE(4, 4, 1, 2) BF_TILE(4, 8, 2, 0)  \
   BF_TILE(4, 4, 2, 0) BF_TILE(4, 2, 2, 0) BF_TILE(4, 2, 1, 0) BF_TILE(4, 1, 1, 0)  \
-  BF_TILE(4, 2, 2, -1) BF_TILE(8, 1, 1, -1)
-#define BF_TILE_LIST_GENERIC BF_TILE(4, 8, 2, 0) BF_TILE(4, 1, 1, 0) BF_TILE(4, 2, 2, -1)
+  BF_TILE(4, 4, 4, 0) BF_TILE(4, 2, 2, -1) BF_TILE(8, 1, 1, -1)
+#define BF_TILE_LIST_GENERIC                                                      \
+  BF_TILE(4, 8, 2, 0) BF_TILE(4, 4, 4, 0) BF_TILE(4, 1, 1, 0) BF_TILE(4, 2, 2, -1)
 // Names for 4-bit input.
 #define BF_TILE_LIST_IN4                                                          \
   BF_TILE(4, 8, 1, 1) BF_TILE(4, 8, 2, 1) BF_TILE(4, 4, 1, 1) BF_TILE(4, 8, 1, 2)  \
   BF_TILE(4, 8, 2, 0) BF_TILE(4, 4, 2, 0) BF_TILE(4, 2, 2, 0) BF_TILE(4, 1, 1, 0)  \
-  BF_TILE(4, 2, 2, -1)
+  BF_TILE(4, 4, 4, 0) BF_TILE(4, 2, 2, -1)
 // Names for complex beam output (16-byte rows; byte-load plans use the
 // generic list).
 #define BF_TILE_LIST_CX                                                           \
   BF_TILE(4, 8, 1, 1) BF_TILE(4, 4, 1, 1) BF_TILE(4, 8, 1, 2) BF_TILE(4, 8, 2, 0)  \
-  BF_TILE(4, 2, 2, 0) BF_TILE(4, 1, 1, 0) BF_TILE(4, 2, 2, -1)
-// Compiled forms.  General (any size; GENERIC is its byte-load list):
+  BF_TILE(4, 2, 2, 0) BF_TILE(4, 1, 1, 0) BF_TILE(4, 4, 4, 0) BF_TILE(4, 2, 2, -1)
+// Compiled forms.  General (any size; BYTES is its byte-load list), with more
+// than two beam tiles per range in 16 bits four in one pass, in FP32 (whose
+// fragments and sums would not fit the registers) two per pass:
 #define BF_TILE_LIST_GENERAL                                                      \
-  BF_TILE(4, 8, 2, 0) BF_TILE(4, 4, 2, 0) BF_TILE(4, 2, 2, 0) BF_TILE(4, 1, 1, 0)  \
-  BF_TILE(4, 2, 2, -1) BF_TILE(8, 1, 1, -1)
+  BF_TILE(4, 8, 2, 0) BF_TILE(4, 4, 2, 0) BF_TILE(4, 4, 4, 0) BF_TILE(4, 2, 2, 0)  \
+  BF_TILE(4, 1, 1, 0) BF_TILE(4, 2, 2, -1) BF_TILE(8, 1, 1, -1)
+#define BF_TILE_LIST_BYTES                                                        \
+  BF_TILE(4, 8, 2, 0) BF_TILE(4, 4, 4, 0) BF_TILE(4, 1, 1, 0) BF_TILE(4, 2, 2, -1)
 // Register-resident pipelined form (2N <= 64):
 #define BF_TILE_LIST_FAST                                                         \
   BF_TILE(4, 8, 1, 1) BF_TILE(4, 6, 1, 1) BF_TILE(4, 4, 1, 1) BF_TILE(4, 2, 1, 1)  \
