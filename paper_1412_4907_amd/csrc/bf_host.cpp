@@ -372,6 +372,16 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
     *out = t;
     *out_sgw = v;
   };
+  if (s.prec != BF_FP32 && s.vec16 && s.mode != kModeGen && need > 1 &&
+      lds_bytes(s.prec, s.Kpad, 2) <= kLdsMax && split_lds_bytes(s.prec, s.Kpad, 2) > kLdsMax) {
+    // N = 552 .. 608: two beam tiles' weights fit LDS only in the general form's
+    // rows, which have no padding per chunk (N = 600 x 27 channels, 256 beams, 7680
+    // samples, FP16, against the streamed form's one tile: I = 64 697 -> 465 us,
+    // I = 16 653 -> 446, I = 1 147 -> 132; I = 5, with dummy rows, 602 -> 671)
+    *out = Tile{4, 2, 2, 0};
+    *out_sgw = choose_sgw(s, *out);
+    return;
+  }
   if (fast_ok(s)) {
     for (const Tile& t : kFastTiles)
       if (s.mode == kModeGen4 || t.nbt == 1) consider(t, t);
@@ -384,8 +394,12 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
   }
   if (found) return;
   Tile t{4, 1, 1, 0};
-  if (lds_bytes(s.prec, s.Kpad, 1) > kLdsMax) {
-    t = Tile{4, 2, 2, -1};  // one beam tile's weights do not fit LDS
+  if (lds_bytes(s.prec, s.Kpad, 1) > (s.vec16 ? kLdsMax : (size_t)80 * 1024)) {
+    // one beam tile's weights do not fit LDS; or they leave one workgroup per
+    // CU, whose four waves wait for each byte of a byte-load row (N = 1121 x 14
+    // channels, 256 beams, FP16: I = 5 12.3 -> 4.6 ms, I = 64 9.6 -> 5.8, I = 1
+    // 1.86 -> 0.89; 16 beams, I = 5: 1.13 -> 0.85; FP32, N = 601: 6.4 -> 2.5)
+    t = Tile{4, 2, 2, -1};
   } else {
     int nbt = s.prec == BF_FP32 ? 8 : 4;
     while (nbt > 1 && (lds_bytes(s.prec, s.Kpad, nbt) > 80 * 1024 || nbt / 2 >= need)) nbt /= 2;

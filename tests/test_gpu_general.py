@@ -123,3 +123,21 @@ def test_channel_past_2gib_equals_two_blocks(gpu, shape, prec):
             half.run(block, want)
             assert torch.equal(got[:, :, k * n:(k + 1) * n], want), (shape, prec, k)
             del block
+
+
+@pytest.mark.parametrize("N,prec", [(1121, "fp16"), (1123, "bf16"), (601, "fp32"), (600, "fp16"),
+                                    (552, "bf16")])
+def test_large_rows_by_default(gpu, N, prec):
+    """Arrays whose default is the general form for its weights' size: byte-load
+    rows with the weights in device memory, and two beam tiles in LDS."""
+    print(f"general large N={N} {prec}", flush=True)
+    C, B, T, I = 2, 40, 96, 16
+    geo = _geometry(N, C, B, N)
+    x = np.random.default_rng(N).integers(-128, 128, (C, T, N, 2)).astype(np.int8)
+    with bf.Plan(N, C, B, T, I, precision=prec) as plan:
+        plan.set_weights(*geo)
+        assert plan.tile()[3] == (-1 if N % 8 else 0)
+        got = run_plan(plan, x, gpu)
+        plan.set_tile(4, 1, 1, 0, 4)
+        assert np.array_equal(run_plan(plan, x, gpu), got)
+    assert_parity(got, oracle.beamform(oracle.weights(*geo), x, I), TOL[prec], f"N={N}")
