@@ -352,9 +352,11 @@ int bf_plan_destroy(bf_plan_t plan);
  * which holds the channels c with c % 8 == XCD index, then helps the
  * others).  Sets whose own tile is the eight-wave streamed form run in a
  * second persistent launch of that form, queued first on the same stream,
- * where they and the other sets each fill the device (else one launch takes
- * them all); when all of those sets read one voltage block, its queues hand out
- * their units channel by channel over the sets.  All
+ * where they and the other sets each fill the device; where every set has
+ * 2N > 128 and they fill it together, that launch may take them all; else the
+ * four-wave launch does.  When all of the eight-wave launch's sets read one
+ * voltage block, its queues hand out their units channel by channel over the
+ * sets.  All
  * plans must share precision, input format and integration class (I == 1,
  * I == 2, or I >= 3) and have their weights set; up to 16 plans.  The batch
  * references the plans (they must outlive it) and owns the device queue

@@ -404,25 +404,9 @@ int fill_sets(const bf_plan_t* plans, int n, const int8_t* const* x, float* cons
     schedule(p->I, p->T, &G, &QI, &SG);
     int32_t sgw;
     if (wide) {
-      // the widest eight-wave beam range whose weights fit the launch's LDS
-      // and that the set's beams fill beyond one narrower range
-      const std::vector<Tile> kWide = bf::wide_tiles();
-      for (int v = 0; v < (int)kWide.size() && variant < 0; ++v) {
-        const Tile& c = kWide[v];
-        if (bf::buffer_shape(*p) && tile_lds(p->prec, p->Kpad, c) <= lds_cap &&
-            (c.nbt == 1 || p->Bpad / 16 > c.nbt / 2))
-          variant = v;
-      }
+      variant = bf::wide_variant(*p, lds_cap, &sgw);
       if (variant < 0) return BF_ERR_UNSUPPORTED;
-      t = kWide[variant];
-      // an eight-wave unit takes as much of the channel's time range as
-      // spreads over its eight waves (at least one MT-aligned step each): no
-      // wave of a unit idles on a short block, and a long block is split into
-      // as few units as that allows, each staging its weights once.  Measured
-      // on a 12-set batch against each set's own count capped the same way:
-      // 19.05-19.10 -> 18.76-18.80 ms.
-      const int32_t base = t.mt / gcd(t.mt, G);
-      sgw = std::max(base, SG / bf::kWideWaves / base * base);
+      t = bf::wide_tiles()[variant];
     } else if (multi) {
       variant = bf::multi_variant(*p, p->asked ? &p->tile : nullptr, lds_cap);
       if (variant < 0) return BF_ERR_UNSUPPORTED;
@@ -1088,29 +1072,18 @@ int bf_batch_run(bf_batch_t bt, const int8_t* const* x, float* const* out, void*
     const bool multi = p0->vec16;
     hipError_t e = queue_ready(&bt->queue, bt->last_use, s);
     if (e != hipSuccess) return from_hip(e);
-    // Sets whose own tile is the streamed form with eight waves run it in a
-    // persistent launch of their own, the others in the four-wave one, where
-    // each launch fills the device by itself; otherwise every set joins the
-    // four-wave launch (two launches run one after the other: 110 against 308 us
-    // for four sets of 10 to 112 channels).
-    int64_t wide_units = 0, four_units = 0;
-    for (int i = 0; i < n && multi; ++i) {
-      const bf_plan_s* p = bt->plans[i];
-      const bool w = bf::form_of(*p, p->tile).kres == bf::kKresStream8;
-      (w ? wide_units : four_units) += units_for(*p, p->tile, p->sgw);
-    }
-    const bool split = wide_units > 0 && wide_units >= 2 * (int64_t)p0->n_cu &&
-                       (four_units == 0 || four_units >= 4 * (int64_t)p0->n_cu);
-    if (multi && split) {
+    bool wide[bf::kMaxProbs];
+    bf::BatchSet sets[bf::kMaxProbs];
+    for (int i = 0; i < n; ++i)
+      sets[i] = bf::BatchSet{bt->plans[i], bt->plans[i]->tile, bt->plans[i]->sgw};
+    if (multi && bf::wide_sets(sets, n, wide)) {
       std::vector<bf_plan_t> wp, rp;
       std::vector<const int8_t*> wx, rx;
       std::vector<float*> wo, ro;
       for (int i = 0; i < n; ++i) {
-        bf_plan_s* p = bt->plans[i];
-        const bool wide = bf::form_of(*p, p->tile).kres == bf::kKresStream8;
-        (wide ? wp : rp).push_back(p);
-        (wide ? wx : rx).push_back(x[i]);
-        (wide ? wo : ro).push_back(out[i]);
+        (wide[i] ? wp : rp).push_back(bt->plans[i]);
+        (wide[i] ? wx : rx).push_back(x[i]);
+        (wide[i] ? wo : ro).push_back(out[i]);
       }
       if (!wp.empty()) {
         Launch LW;

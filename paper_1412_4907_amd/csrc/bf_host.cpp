@@ -436,6 +436,45 @@ int multi_variant(const Shape& s, const Tile* own, size_t lds_cap) {
   return -1;
 }
 
+int wide_variant(const Shape& s, size_t lds_cap, int32_t* sgw) {
+  const int n = (int)(sizeof(kWideTiles) / sizeof(kWideTiles[0]));
+  for (int v = 0; v < n; ++v) {
+    const Tile& c = kWideTiles[v];
+    if (!buffer_shape(s) || tile_lds(s.prec, s.Kpad, c) > lds_cap ||
+        (c.nbt > 1 && s.Bpad / 16 <= c.nbt / 2))
+      continue;
+    int32_t G, QI, SG;
+    schedule(s.I, s.T, &G, &QI, &SG);
+    const int32_t base = c.mt / gcd(c.mt, G);
+    *sgw = std::max(base, SG / kWideWaves / base * base);
+    return v;
+  }
+  return -1;
+}
+
+bool wide_sets(const BatchSet* sets, int n, bool* wide) {
+  int64_t want = 0, others = 0, cramped = 0;
+  bool all = true;
+  const int n_cu = n > 0 ? sets[0].s->n_cu : 256;
+  for (int i = 0; i < n; ++i) {
+    const Shape& s = *sets[i].s;
+    wide[i] = form_of(s, sets[i].tile).kres == kKresStream8;
+    (wide[i] ? want : others) += units_for(s, sets[i].tile, sets[i].sgw);
+    int32_t sgw = 0;
+    const int v = wide_variant(s, kLdsMax, &sgw);
+    all = all && v >= 0 && s.Kpad > 2 * kChunk;
+    if (v >= 0 && s.Bpad > 32 && split_lds_bytes(s.prec, s.Kpad, 4) > 80 * 1024)
+      cramped += units_for(s, kWideTiles[v], sgw);
+  }
+  const bool short_steps = sets[0].s->mode == kModeI1 || sets[0].s->mode == kModeGen4;
+  if (all && (want >= 2 * (int64_t)n_cu || (sets[0].s->prec != BF_FP32 && short_steps &&
+                                            4 * cramped >= 3 * (int64_t)n_cu))) {
+    for (int i = 0; i < n; ++i) wide[i] = true;
+    return true;
+  }
+  return want >= 2 * (int64_t)n_cu && (others == 0 || others >= 4 * (int64_t)n_cu);
+}
+
 int check_tile(const Shape& s, Tile t, int32_t sgw) {
   if (sgw < 1) return BF_ERR_INVALID_ARG;
   if (!tile_ok(s, t)) return BF_ERR_UNSUPPORTED;

@@ -98,6 +98,34 @@ bool wide_shape(const Shape& s);
 // form (null: none asked for), else the widest beam range the set's beams fill
 // that leaves two workgroups per CU; -1: none.
 int multi_variant(const Shape& s, const Tile* own, size_t lds_cap);
+// The eight-wave batching variant (index into BF_TILE_LIST_WIDE) for a set: the
+// widest beam range whose weights fit lds_cap and that the set's beams fill
+// beyond one of half the width; -1: none.  *sgw: its store groups per wave: as
+// much of the channel's time range as spreads over the eight waves (at least one
+// MT-aligned step each), so that no wave of a unit idles on a short block and a
+// long block is split into as few units as that allows, each staging its
+// weights once (a 12-set batch against each set's own count capped the same
+// way: 19.05-19.10 -> 18.76-18.80 ms).
+int wide_variant(const Shape& s, size_t lds_cap, int32_t* sgw);
+// A set of a batch and its plan's tile.
+struct BatchSet {
+  const Shape* s;
+  Tile tile;
+  int32_t sgw;
+};
+// Which sets of a batch (16-byte rows) run in a persistent launch of the
+// eight-wave streamed form, the others in the four-wave launch behind it.  True
+// if any does.
+// One launch of the eight-wave form takes them all where every set has more than
+// two chunks of K and either the sets whose own tile it is have two units per CU
+// (FP32, N 256 / 256 / 304, 64, 16 and 8 channels, I = 16: 834 -> 403 us), or, in
+// 16 bits at I == 1 or I % 4 == 0, the sets for whose four beam tiles two
+// four-wave workgroups do not fit a CU make up 3/4 unit per CU there (N 200 and
+// 256, 32 channels, FP16: I = 16 143 -> 109 us, I = 64 151 -> 135, I = 1 185 both;
+// with 64 units of N = 256 the four-wave launch stays: 41 against 59).
+// Else two launches, where both fill the device several times: each drains on
+// its own (four sets of 10 to 112 channels: 308 us split, 110 together).
+bool wide_sets(const BatchSet* sets, int n, bool* wide);
 // Modelled cycles of one unit of form f with v store groups per wave.
 double unit_cycles(const Shape& s, Tile f, int32_t v, int wg);
 

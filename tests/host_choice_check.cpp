@@ -55,8 +55,65 @@ static int check_large_arrays() {
   return 0;
 }
 
+struct Set {
+  int N, C, B, W;
+  bool stream8;  // asks for tile (4, 1, 1, -3, 4)
+};
+
+// 0: no set in the eight-wave launch, 1: some, 2: all
+static int wide_of(const Set* sets, int n, int I, int prec) {
+  Shape s[16];
+  bf::BatchSet b[16];
+  bool wide[16];
+  for (int i = 0; i < n; ++i) {
+    if (bf::make_shape(sets[i].N, sets[i].C, sets[i].B, (int64_t)sets[i].W * I, I, prec, 0, 256,
+                       &s[i]) != BF_OK)
+      return -1;
+    b[i].s = &s[i];
+    if (sets[i].stream8) {
+      b[i].tile = Tile{4, 1, 1, -3};
+      b[i].sgw = 4;
+      if (bf::check_tile(s[i], b[i].tile, 4) != BF_OK) return -1;
+    } else {
+      bf::choose_tile(s[i], &b[i].tile, &b[i].sgw);
+    }
+  }
+  if (!bf::wide_sets(b, n, wide)) return 0;
+  int k = 0;
+  for (int i = 0; i < n; ++i) k += wide[i];
+  return k == n ? 2 : 1;
+}
+
+// The batches of tests/test_gpu_batch_wide.py take the eight-wave launch; and the
+// shapes the rule was drawn from.
+static int check_wide_batches() {
+  const Set all[] = {{136, 520, 16, 32, true}, {200, 520, 10, 20, true}};
+  const Set mixed[] = {{136, 520, 16, 32, true}, {200, 520, 10, 20, true},
+                       {16, 1030, 16, 32, false}, {32, 1030, 30, 6, false}};
+  const Set shared[] = {{136, 520, 16, 32, true}, {136, 520, 40, 32, true},
+                        {136, 520, 5, 32, true}};
+  for (int prec : {BF_FP16, BF_BF16, BF_FP32})
+    for (int I : {1, 2, 10, 16}) {
+      CHECK(wide_of(all, 2, I, prec) == 2);
+      CHECK(wide_of(mixed, 4, I, prec) == 1);
+      CHECK(wide_of(shared, 3, I, prec) == 2);
+    }
+  const Set pair[] = {{200, 32, 300, 240, false}, {256, 32, 100, 240, false}};
+  CHECK(wide_of(pair, 2, 16, BF_FP16) == 2);
+  const Set one[] = {{256, 64, 64, 120, false}};
+  CHECK(wide_of(one, 1, 16, BF_FP16) == 0);
+  const Set tiny[] = {{256, 8, 64, 1920, false}};
+  CHECK(wide_of(tiny, 1, 1, BF_FP16) == 0);
+  const Set f32[] = {{256, 64, 300, 240, false}, {256, 16, 16, 60, false}, {304, 8, 40, 60, false}};
+  CHECK(wide_of(f32, 3, 16, BF_FP32) == 2);
+  const Set small_mix[] = {{120, 8, 151, 1762, false}, {160, 9, 394, 93, false},
+                           {24, 101, 344, 263, false}, {200, 77, 18, 239, false}};
+  CHECK(wide_of(small_mix, 4, 8, BF_BF16) == 0);
+  return 0;
+}
+
 int main() {
-  if (check_large_arrays()) return 1;
+  if (check_large_arrays() || check_wide_batches()) return 1;
   std::printf("OK %d checks\n", g_checks);
   return 0;
 }
