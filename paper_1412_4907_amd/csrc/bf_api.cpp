@@ -119,7 +119,7 @@ Prob make_prob(const bf_plan_s* p, const Tile& form, int32_t sgw, const int8_t* 
   q.G = G;
   q.QI = QI;
   q.SG = SG;
-  q.sgw = sgw;
+  q.sgw = sgw = bf::wave_sgw(*p, form, sgw);
   // the plan's beam tiles spread evenly over as few ranges as the form's
   // width allows: 9 tiles at width 4 run as 3 + 3 + 3 (measured in choose_tile)
   const int32_t need = p->Bpad / 16;

@@ -1,6 +1,7 @@
 // bf_host.cpp -- host-side logic with no HIP dependency (see bf_host.h).
 #include "bf_host.h"
 
+#include <algorithm>
 #include <cctype>
 #include <cmath>
 #include <cstdio>
@@ -139,26 +140,47 @@ bool same_tile(const Tile& a, const Tile& b) {
   return a.mt == b.mt && a.nbt == b.nbt && a.nbp == b.nbp && a.kres == b.kres;
 }
 
-// Byte offsets within one channel's voltages (rows up to the last wave step's
-// and store group's padding, plus the out-of-range marker 2^31 added to them)
-// and one channel's output rows must fit 32 bits.
-bool buffer_shape(const Shape& s) {
+// Bytes of voltages one wave reaches over with v store groups: its own rows and
+// those up to the last wave step's and store group's padding (I % 4 != 0: a
+// step can reach into the store group behind the last one).
+static int64_t wave_span(const Shape& s, int64_t v) {
   const int64_t rowb = s.in4 ? s.N : 2 * (int64_t)s.N;
-  const int64_t out = s.cx ? s.T : s.T / s.I;  // 4 bytes each
-  // I % 4 != 0: a step can reach into the store group behind the last one
   const int64_t pad = (s.mode == kModeGen ? 32 : 16) * (int64_t)s.I + 128;
-  return s.T < ((int64_t)1 << 31) && (s.T + pad) * rowb < 0x7FFFFF00 &&
-         (int64_t)s.B * out * 4 < 0x7FFFFF00;
+  return (std::min(s.T, v * 16 * s.I) + pad) * rowb;
+}
+constexpr int64_t kSpanMax = 0x7FFFFF00;  // below the out-of-range marker 2^31
+
+// sgw * (row tiles per store group) must be a multiple of MT
+static int32_t base_sgw(const Shape& s, int32_t mt) {
+  int32_t G, QI, SG;
+  schedule(s.I, s.T, &G, &QI, &SG);
+  return mt / gcd(mt, G);
+}
+
+bool buffer_shape(const Shape& s, int nbt) {
+  const int64_t out = s.cx ? s.T : s.T / s.I;  // 4 bytes each
+  return s.T < ((int64_t)1 << 31) && wave_span(s, base_sgw(s, 4)) < kSpanMax &&
+         std::min((int64_t)s.B, (int64_t)16 * nbt) * out * 4 < kSpanMax;
+}
+
+int32_t wave_sgw(const Shape& s, const Tile& f, int32_t sgw) {
+  if (f.kres == 0 || f.kres == -1 || wave_span(s, sgw) < kSpanMax) return sgw;
+  const int64_t rowb = s.in4 ? s.N : 2 * (int64_t)s.N;
+  const int32_t base = base_sgw(s, f.mt);
+  const int64_t most = (kSpanMax - 1 - wave_span(s, 0)) / (16 * s.I * rowb);
+  return (int32_t)std::max<int64_t>(base, most / base * base);
 }
 
 bool wide_shape(const Shape& s) {
   if (s.prec == BF_FP32 || s.cx || !s.vec16 || (s.flags & BF_ACCUMULATE)) return false;
   if (s.mode != kModeI1 && s.mode != kModeGen4) return false;
-  return (s.T / s.I) % 4 == 0 && buffer_shape(s);
+  // the whole channel and all its beams within one wave's reach
+  return (s.T / s.I) % 4 == 0 && s.T < ((int64_t)1 << 31) && wave_span(s, s.T) < kSpanMax &&
+         (int64_t)s.B * (s.T / s.I) * 4 < kSpanMax;
 }
 
 bool fast_ok(const Shape& s) {
-  if (s.Kpad != kChunk || s.N % 2 != 0 || !buffer_shape(s)) return false;
+  if (s.Kpad != kChunk || s.N % 2 != 0 || !buffer_shape(s, 1)) return false;
   if (s.mode == kModeGen4) return true;
   // I == 1 and complex beams: one beam tile, overwriting, whole 16-byte quads.
   // Wider ranges store tile by tile between MFMA phases here and are bound by
@@ -172,10 +194,9 @@ bool fast_ok(const Shape& s) {
 // and whose weights fit.  Four waves while two workgroups fit a CU (one
 // stages its weights while the other computes), else eight.
 bool stream_tile(const Shape& s, size_t lds_cap, Tile* t) {
-  if (!buffer_shape(s)) return false;
   const int need = s.Bpad / 16;
   for (int nbt = 4; nbt >= 1; nbt /= 2) {
-    if (nbt > 1 && nbt / 2 >= need) continue;
+    if ((nbt > 1 && nbt / 2 >= need) || !buffer_shape(s, nbt)) continue;
     const size_t l = split_lds_bytes(s.prec, s.Kpad, nbt);
     if (l > lds_cap) continue;
     *t = Tile{4, nbt, nbt, l <= 80 * 1024 ? kKresStream4 : kKresStream8};
@@ -192,7 +213,8 @@ Tile form_of(const Shape& s, Tile t) {
     return Tile{4, nbt, nbt, kKresStream8};
   }
   if (t.kres >= 1) {
-    if (t.kres == 1 && fast_ok(s)) return Tile{4, s.mode == kModeGen4 ? t.nbt : 1, 1, 1};
+    if (t.kres == 1 && fast_ok(s) && buffer_shape(s, s.mode == kModeGen4 ? t.nbt : 1))
+      return Tile{4, s.mode == kModeGen4 ? t.nbt : 1, 1, 1};
     Tile r;
     if (stream_tile(s, kLdsMax, &r)) return r;
     t.kres = 0;
@@ -217,7 +239,7 @@ std::vector<Tile> compiled_tiles(const Shape& s) {
     v = as_vector(kGenTiles);
   if (fast_ok(s))
     for (const Tile& t : kFastTiles) {
-      bool named = s.mode != kModeGen4 && t.nbt > 1;
+      bool named = (s.mode != kModeGen4 && t.nbt > 1) || !buffer_shape(s, t.nbt);
       for (const Tile& o : v) named = named || same_tile(o, t);
       if (!named) v.push_back(t);
     }
@@ -225,10 +247,10 @@ std::vector<Tile> compiled_tiles(const Shape& s) {
     v.push_back(Tile{4, 4, 4, kKresWide});
     v.push_back(Tile{4, 2, 2, kKresWide});
   }
-  if (buffer_shape(s))
-    for (const Tile& t : kStreamTiles)
-      // the eight-wave ranges that kres == -2 names are not offered twice
-      if (!(t.kres == kKresStream8 && t.nbt > 1 && wide_shape(s))) v.push_back(t);
+  for (const Tile& t : kStreamTiles)
+    // the eight-wave ranges that kres == -2 names are not offered twice
+    if (buffer_shape(s, t.nbt) && !(t.kres == kKresStream8 && t.nbt > 1 && wide_shape(s)))
+      v.push_back(t);
   return v;
 }
 
@@ -256,7 +278,7 @@ int64_t units_for(const Shape& s, Tile t, int32_t sgw) {
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
   const int64_t nbr = (s.Bpad / 16 + f.nbt - 1) / f.nbt;
-  const int64_t per = (int64_t)waves_of(f) * sgw;
+  const int64_t per = (int64_t)waves_of(f) * wave_sgw(s, f, sgw);
   const int64_t ntr = (SG + per - 1) / per;
   return (int64_t)s.C * nbr * ntr;
 }
@@ -321,15 +343,20 @@ static double form_cycles(const Shape& s, const Tile& f, int32_t v) {
 // -> 85 us.  Per-sample outputs (I == 1, complex) are bound by the write stream,
 // which reaches HBM better in short runs: at most 16 groups, 4 for one beam tile
 // (N = 32, 512 beams, I = 1: 218 us at 16, 222 at 32, 245 at 8; 16 complex
-// beams: 762 at 4, 786 at 8, 816 at 32).
+// beams: 762 at 4, 786 at 8, 816 at 32).  The general form at one chunk, which
+// runs where rows are over 100 MB apart: 64 (N = 32, 64 beams, 35.6 M samples: 2.67
+// to 2.86 ms at 16, 2.64 at 32 and 64, 2.78 at 256).
 static int32_t best_sgw(const Shape& s, const Tile& f, int32_t base, double* cycles) {
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
-  const int32_t most = s.I > 1 ? 1 << 20 : f.nbt == 1 ? 4 : 16;
+  const int32_t most = s.I > 1 ? 1 << 20
+                       : f.kres == 0 && s.Kpad == kChunk ? 64
+                       : f.nbt == 1 ? 4 : 16;
   int32_t best = base;
   for (int32_t k = 1;; k = k < 4 ? k + 1 : k + k / 3) {
     if ((int64_t)base * k > most) break;
     const int32_t v = base * k;
+    if (wave_sgw(s, f, v) != v) break;
     const double c = form_cycles(s, f, v);
     if (k == 1 || c < *cycles) {
       best = v;
@@ -340,16 +367,9 @@ static int32_t best_sgw(const Shape& s, const Tile& f, int32_t base, double* cyc
   return best;
 }
 
-// sgw * (row tiles per store group) must be a multiple of MT
-static int32_t base_sgw(const Shape& s, const Tile& t) {
-  int32_t G, QI, SG;
-  schedule(s.I, s.T, &G, &QI, &SG);
-  return t.mt / gcd(t.mt, G);
-}
-
 int32_t choose_sgw(const Shape& s, Tile t) {
   double cycles = 0;
-  return best_sgw(s, form_of(s, t), base_sgw(s, t), &cycles);
+  return best_sgw(s, form_of(s, t), base_sgw(s, t.mt), &cycles);
 }
 
 // Default tile: the register-resident form (2N <= 64) or the streamed form (up
@@ -365,7 +385,7 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
     if (tile_lds(s.prec, s.Kpad, f) > kLdsMax) return;
     if (f.nbt > 1 && f.kres != 1 && f.nbt / 2 >= need) return;
     double c = 0;
-    const int32_t v = best_sgw(s, f, base_sgw(s, t), &c);
+    const int32_t v = best_sgw(s, f, base_sgw(s, t.mt), &c);
     if (found && c >= least) return;
     found = true;
     least = c;
@@ -382,10 +402,26 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
     *out_sgw = choose_sgw(s, *out);
     return;
   }
+  // Where the output rows of the whole beam range do not fit the offsets (up to
+  // four beam tiles; few samples per window, a channel past 2 GiB), narrower
+  // ranges would read the voltages again for each: the register-resident form
+  // takes the widest that fits (64 beams, FP16: N = 32 at I = 4 1.52 -> 1.29 ms, N = 8 at
+  // I = 16 3.0, 4.7 in the general form), in 16 bits the general form's 64-bit rows
+  // are faster than a narrower streamed one (N = 32 at I = 2 2.10 -> 1.49, N = 64 at I = 1
+  // 1.91 -> 1.38; FP32 stays: N = 32 at I = 2 2.06 against 2.51).
+  int range = 1, widest = 1;
+  while (range < 4 && range < need) range *= 2;
+  const bool narrow = !buffer_shape(s, range);
+  for (const Tile& t : kFastTiles)
+    if (t.nbt > widest && buffer_shape(s, t.nbt)) widest = t.nbt;
   if (fast_ok(s)) {
     for (const Tile& t : kFastTiles)
-      if (s.mode == kModeGen4 || t.nbt == 1) consider(t, t);
-  } else if (buffer_shape(s) && s.Kpad <= 2048) {
+      if ((s.mode == kModeGen4 || t.nbt == 1) && t.nbt <= widest && (!narrow || t.nbt == widest))
+        consider(t, t);
+  } else if (narrow && s.prec != BF_FP32 && s.vec16 &&
+             lds_bytes(s.prec, s.Kpad, range) <= 80 * 1024) {
+    // the general form, below
+  } else if (s.Kpad <= 2048) {
     for (const Tile& f : kStreamTiles) {
       Tile t = f;
       if (f.kres == kKresStream8 && f.nbt > 1 && wide_shape(s)) t.kres = kKresWide;
@@ -418,8 +454,8 @@ int multi_variant(const Shape& s, const Tile* own, size_t lds_cap) {
   const int n = (int)(sizeof(kMultiTiles) / sizeof(kMultiTiles[0]));
   auto runs = [&](const Tile& c, size_t cap) {
     if (tile_lds(s.prec, s.Kpad, c) > cap) return false;
-    if (c.kres == 1) return s.mode == kModeGen4 && fast_ok(s);
-    return c.kres == kKresStream4 ? buffer_shape(s) : true;
+    if (c.kres == 1) return s.mode == kModeGen4 && fast_ok(s) && buffer_shape(s, c.nbt);
+    return c.kres == kKresStream4 ? buffer_shape(s, c.nbt) : true;
   };
   const Tile f = own ? form_of(s, *own) : Tile{0, 0, 0, 0};
   const int need = s.Bpad / 16;
@@ -440,7 +476,7 @@ int wide_variant(const Shape& s, size_t lds_cap, int32_t* sgw) {
   const int n = (int)(sizeof(kWideTiles) / sizeof(kWideTiles[0]));
   for (int v = 0; v < n; ++v) {
     const Tile& c = kWideTiles[v];
-    if (!buffer_shape(s) || tile_lds(s.prec, s.Kpad, c) > lds_cap ||
+    if (!buffer_shape(s, c.nbt) || tile_lds(s.prec, s.Kpad, c) > lds_cap ||
         (c.nbt > 1 && s.Bpad / 16 <= c.nbt / 2))
       continue;
     int32_t G, QI, SG;

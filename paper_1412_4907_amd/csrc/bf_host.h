@@ -60,8 +60,13 @@ size_t tile_lds(int prec, int32_t Kpad, Tile t);
 void schedule(int32_t I, int64_t T, int32_t* G, int32_t* QI, int32_t* SG);
 bool same_tile(const Tile& a, const Tile& b);
 // Whether the shape's byte offsets fit the 32-bit buffer offsets of the
-// register-resident and streamed forms.
-bool buffer_shape(const Shape& s);
+// register-resident and streamed forms at a width of nbt beam tiles: they count
+// from a wave's first voltage row (over as few store groups as it may have) and
+// from a beam range's first output row, so a channel may be longer.
+bool buffer_shape(const Shape& s, int nbt);
+// The store groups per wave of a run under form f where sgw are asked for: as
+// many of them as its offsets reach.
+int32_t wave_sgw(const Shape& s, const Tile& f, int32_t sgw);
 // Whether the register-resident form (2N <= 64) can run the shape.
 bool fast_ok(const Shape& s);
 // The streamed form's tile for the shape (BF_TILE_LIST_STREAM), with weights

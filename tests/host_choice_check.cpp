@@ -1,6 +1,7 @@
 // Choices of the host logic whose lines were drawn by measurement, built for the
 // CPU (tests/test_host_choice.py).  Prints "OK ..." and exits 0, or names the
 // first failed check and exits 1.
+#include <algorithm>
 #include <cstdio>
 
 #include "bf_host.h"
@@ -112,8 +113,53 @@ static int check_wide_batches() {
   return 0;
 }
 
+// Channels past 2 GiB: offsets count from a wave's first row and a beam range's
+// first output row.
+static int check_long_channels() {
+  const int64_t T = 35651520;  // 32 antennas: 2.28 GB
+  int32_t sgw = 0;
+  Tile t = chosen(32, 1, 64, T, 16, BF_FP16, 0, &sgw);
+  CHECK(t.kres == 1 && t.nbt > 1);
+  t = chosen(32, 1, 64, T, 10, BF_BF16);
+  CHECK(t.kres == bf::kKresStream4 && t.nbt == 4);
+  CHECK(chosen(33, 1, 64, T, 16, BF_FP16).kres < -1);
+  CHECK(chosen(32, 1, 64, 2 * T, 16, BF_FP16, BF_INPUT_4BIT).kres == 1);
+  // 64 output rows past the offsets: 64-bit rows in 16 bits, narrower ranges else
+  for (int I : {1, 2}) CHECK(chosen(32, 1, 64, T, I, BF_FP16).kres == 0);
+  CHECK(chosen(32, 1, 64, T, 2, BF_FP32).kres == bf::kKresStream4);
+  t = chosen(32, 1, 64, T, 4, BF_FP16);
+  CHECK(t.kres == 1 && t.nbt == 2);
+  t = chosen(8, 1, 64, 142606080, 16, BF_FP16);
+  CHECK(t.kres == 1 && t.nbt == 2);
+  // store groups per wave: as asked for while the channel fits, else as many as
+  // the offsets reach, in whole wave steps
+  int cut = 0;
+  for (int N : {1, 8, 32, 33, 256, 4096})
+    for (int I : {1, 2, 3, 16, 1000})
+      for (int64_t T1 : {(int64_t)6000, (int64_t)6000000, (int64_t)1500000000})
+        for (int B : {1, 64}) {
+          Shape s;
+          if (bf::make_shape(N, 1, B, T1, I, BF_FP16, 0, 256, &s) != BF_OK) continue;
+          for (int nbt : {1, 4}) {
+            if (!bf::buffer_shape(s, nbt)) continue;
+            const Tile f{4, nbt, nbt, bf::kKresStream4};
+            const int32_t base = I == 1 ? 4 : I == 2 ? 2 : 1;
+            for (int32_t g : {base, 12, 1 << 20}) {
+              const int32_t v = bf::wave_sgw(s, f, g);
+              CHECK(v >= base && v <= g && (v == g || v % base == 0));
+              const int64_t rows = std::min(T1, (int64_t)v * 16 * I);
+              CHECK((rows + 16 * (int64_t)I) * 2 * N < ((int64_t)1 << 31));
+              CHECK(std::min(B, 16 * nbt) * (T1 / I) * 4 < ((int64_t)1 << 31));
+              cut += v < g;
+            }
+          }
+        }
+  CHECK(cut > 20);
+  return 0;
+}
+
 int main() {
-  if (check_large_arrays() || check_wide_batches()) return 1;
+  if (check_large_arrays() || check_wide_batches() || check_long_channels()) return 1;
   std::printf("OK %d checks\n", g_checks);
   return 0;
 }

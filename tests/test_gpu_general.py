@@ -93,6 +93,7 @@ FAR = [
     (64, 33, 16_800_000, 2, 8, "power"), (33, 17, 32_640_000, 16, 8, "power"),
     (256, 20, 4_200_000, 1, 8, "power"), (32, 40, 67_200_000, 16, 4, "power"),
     (40, 5, 27_000_000, 1, 8, "complex"), (40, 24, 54_000_000, 3, 4, "power"),
+    (32, 20, 33_600_000, 1, 8, "power"),  # 16 output rows past 2 GiB too: general
 ]
 
 
@@ -116,6 +117,14 @@ def test_channel_past_2gib_equals_two_blocks(gpu, shape, prec):
                 p.set_output_scale(1 / 64)
         got = torch.empty(far.p_shape, dtype=far.p_dtype, device=gpu)
         far.run(x, got)
+        streamed = [t for t in far.tile_candidates() if t[3] == -4]
+        assert bool(streamed) == (T // I * 4 * min(B, 16) < 2 ** 31 - 256)
+        if streamed:  # work units longer than a wave's offsets reach
+            far.set_tile(*streamed[-1], 1 << 20)
+            longest = torch.empty_like(got)
+            far.run(x, longest)
+            assert torch.equal(longest, got)
+            del longest
         want = torch.empty(half.p_shape, dtype=half.p_dtype, device=gpu)
         n = half.p_shape[2]
         for k in range(2):
