@@ -326,7 +326,9 @@ int bf_plan_set_tile(bf_plan_t plan, int32_t mt, int32_t nbt, int32_t nbp, int32
 int bf_plan_set_output_scale(bf_plan_t plan, float scale);
 
 /*
- * List the compiled tile variants that can run this plan: writes up to
+ * List the tile variants that can run this plan, one name for each compiled
+ * form (bf_plan_set_tile and tile caches also take the other names that earlier
+ * forms had): writes up to
  * max_tiles rows of (mt, nbt, nbp, kres) into tiles[][4] and returns how
  * many exist (which may exceed max_tiles; tiles may be NULL when
  * max_tiles == 0), or BF_ERR_INVALID_ARG.

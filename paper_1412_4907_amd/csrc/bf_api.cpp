@@ -986,19 +986,21 @@ int bf_plan_set_output_scale(bf_plan_t p, float scale) {
 
 int bf_plan_tile_candidates(bf_plan_t p, int32_t* tiles, int32_t max_tiles) {
   if (!p || max_tiles < 0 || (max_tiles > 0 && !tiles)) return BF_ERR_INVALID_ARG;
-  int32_t n = 0;
-  auto add = [&](const Tile& t) {
-    if (!tile_ok(*p, t)) return;
-    if (n < max_tiles) {
-      tiles[4 * n + 0] = t.mt;
-      tiles[4 * n + 1] = t.nbt;
-      tiles[4 * n + 2] = t.nbp;
-      tiles[4 * n + 3] = t.kres;
+  try {
+    int32_t n = 0;
+    for (const Tile& t : bf::offered_tiles(*p)) {
+      if (n < max_tiles) {
+        tiles[4 * n + 0] = t.mt;
+        tiles[4 * n + 1] = t.nbt;
+        tiles[4 * n + 2] = t.nbp;
+        tiles[4 * n + 3] = t.kres;
+      }
+      ++n;
     }
-    ++n;
-  };
-  for (const Tile& t : bf::compiled_tiles(*p)) add(t);
-  return n;
+    return n;
+  } catch (...) {
+    return BF_ERR_OOM;
+  }
 }
 
 int bf_batch_tile_candidates(bf_plan_t p, int32_t* tiles, int32_t max_tiles) {

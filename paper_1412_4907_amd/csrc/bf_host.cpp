@@ -273,6 +273,22 @@ bool tile_ok(const Shape& s, Tile t) {
   return tile_lds(s.prec, s.Kpad, form_of(s, t)) <= kLdsMax;
 }
 
+std::vector<Tile> offered_tiles(const Shape& s) {
+  std::vector<Tile> names, offered;
+  for (const Tile& t : compiled_tiles(s))
+    if (tile_ok(s, t)) names.push_back(t);
+  for (size_t i = 0; i < names.size(); ++i) {
+    const Tile f = form_of(s, names[i]);
+    const bool own = same_tile(names[i], f);
+    bool first = true;
+    for (size_t j = 0; j < names.size() && first; ++j)
+      if (j != i && same_tile(form_of(s, names[j]), f))
+        first = own || (j > i && !same_tile(names[j], f));
+    if (first) offered.push_back(names[i]);
+  }
+  return offered;
+}
+
 int64_t units_for(const Shape& s, Tile t, int32_t sgw) {
   const Tile f = form_of(s, t);
   int32_t G, QI, SG;

@@ -91,6 +91,10 @@ void choose_tile(const Shape& s, Tile* t, int32_t* sgw);
 int check_tile(const Shape& s, Tile t, int32_t sgw);
 // Every single-set tile compiled for the shape's form, in list order.
 std::vector<Tile> compiled_tiles(const Shape& s);
+// One name for each form that runs the shape: the form's own where it has one.
+// (An FP16 plan of 32 antennas at I = 1 has 20 names for 12 forms; timing all of
+// them would time one kernel eight times and keep its luckiest run.)
+std::vector<Tile> offered_tiles(const Shape& s);
 // The variants the persistent batching kernel carries.
 std::vector<Tile> multi_tiles();
 // Variants of the eight-wave batching kernels (BF_TILE_LIST_WIDE order).

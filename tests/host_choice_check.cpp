@@ -3,6 +3,7 @@
 // first failed check and exits 1.
 #include <algorithm>
 #include <cstdio>
+#include <vector>
 
 #include "bf_host.h"
 
@@ -158,7 +159,41 @@ static int check_long_channels() {
   return 0;
 }
 
+// Tile candidates: one name per form, and every form that a name stands for.
+static int check_offered() {
+  int fewer = 0;
+  for (int prec = 0; prec < 3; ++prec)
+    for (int N : {1, 16, 32, 33, 40, 64, 256, 600, 1248, 4096})
+      for (int B : {4, 33, 128, 512})
+        for (int I : {1, 2, 5, 16})
+          for (uint32_t fl : {0u, (uint32_t)BF_ACCUMULATE, (uint32_t)BF_INPUT_4BIT,
+                              (uint32_t)BF_OUTPUT_COMPLEX}) {
+            Shape s;
+            if (bf::make_shape(N, 3, B, 4800, I, prec, fl, 256, &s) != BF_OK) continue;
+            const std::vector<Tile> v = bf::offered_tiles(s);
+            CHECK(!v.empty());
+            for (size_t i = 0; i < v.size(); ++i) {
+              CHECK(bf::tile_ok(s, v[i]));
+              for (size_t j = 0; j < i; ++j)
+                CHECK(!bf::same_tile(bf::form_of(s, v[i]), bf::form_of(s, v[j])));
+            }
+            size_t names = 0;
+            for (const Tile& t : bf::compiled_tiles(s)) {
+              if (!bf::tile_ok(s, t)) continue;
+              ++names;
+              bool there = false;
+              for (const Tile& o : v)
+                there = there || bf::same_tile(bf::form_of(s, t), bf::form_of(s, o));
+              CHECK(there);
+            }
+            fewer += v.size() < names;
+          }
+  CHECK(fewer > 100);
+  return 0;
+}
+
 int main() {
+  if (check_offered()) return 1;
   if (check_large_arrays() || check_wide_batches() || check_long_channels()) return 1;
   std::printf("OK %d checks\n", g_checks);
   return 0;

@@ -44,7 +44,8 @@ def test_every_width_equals_the_default(gpu, shape, prec):
             want = run_plan(plan, x, gpu)
             assert np.all(np.isinf(want[1, 3]) | np.isnan(want[1, 3])) == overflow
             tiles = [t for t in plan.tile_candidates() if t[3] in (0, -1)]
-            assert {(4, 4, 4, 0), (4, 1, 1, 0), (4, 2, 2, -1)} <= set(tiles)
+            wide = (4, 4, 2, 0) if prec == "fp32" else (4, 4, 4, 0)  # passes of two tiles, of four
+            assert {wide, (4, 1, 1, 0), (4, 2, 2, -1)} <= set(tiles)
             default = plan.tile()
             for t in tiles:
                 plan.set_tile(*t, 8)
