@@ -38,7 +38,11 @@
  *   BF_FP32  weights rounded from FP64 to FP32 and held in FP32; each enters
  *            the products as its exact sum of three BF16 values, the voltages
  *            exactly as BF16, so every product is exact and only the FP32
- *            accumulation (BF16 MFMA) rounds.
+ *            accumulation (BF16 MFMA) rounds.  Exact from 2^-110 on; what a
+ *            smaller weight loses (below 2^-133) reaches no output: power is
+ *            below FP32's range there, and complex output at a scale from
+ *            2^60 on, with no weight of 2^80 or more in the plan, splits its
+ *            weights times 2^24.
  *   BF_FP16  weights rounded from FP64 to FP16 (round to nearest even, one
  *            rounding); voltages converted exactly to FP16; FP16 MFMA with
  *            FP32 accumulation.

@@ -32,6 +32,8 @@ struct bf_plan_s : bf::Shape {
   int device = 0;
   size_t w_bytes = 0;
   void* w_dev = nullptr;  // the weights runs read
+  // the largest weight component's magnitude in w_dev and w_alt
+  double w_max = 1.0, w_max_alt = 1.0;
   bool weights_set = false;
   // geometry staging for bf_set_weights: pinned host + device, reused
   // (positions, directions, frequencies, antenna mask)
@@ -134,6 +136,14 @@ Prob make_prob(const bf_plan_s* p, const Tile& form, int32_t sgw, const int8_t* 
   // units run together, whereas one beam range's weights are small
   q.br_fast = q.nbr > 1 ? 1 : 0;
   q.out_scale = p->out_scale;
+  q.w_scale = 1.0f;
+  // FP32 weights below 2^-110 are not the sum of three BF16 values; their beams
+  // reach FP16 only through a scale past 2^60.  Sums of 8192 products of a weight
+  // and a voltage stay below 2^128 at 2^24 times 2^80.
+  if (p->cx && p->prec == BF_FP32 && p->out_scale >= 0x1p60f && p->w_max < 0x1p80) {
+    q.w_scale = 0x1p24f;
+    q.out_scale = p->out_scale * 0x1p-24f;
+  }
   return q;
 }
 
@@ -499,6 +509,7 @@ hipError_t take_refresh(bf_plan_s* p, hipStream_t s) {
   if (e != hipSuccess) return e;
   std::swap(p->w_dev, p->w_alt);
   std::swap(p->used_cur, p->used_alt);
+  std::swap(p->w_max, p->w_max_alt);
   p->refresh_pending = false;
   p->weights_set = true;
   return hipSuccess;
@@ -698,6 +709,7 @@ int bf_set_weights(bf_plan_t p, const double* pos, const double* dir, const doub
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int st = generate_weights(p, pos, dir, freq, p->w_dev, s);
     if (st != BF_OK) return st;
+    p->w_max = 1.0;
     p->refresh_pending = false;  // superseded
     p->weights_set = true;
     return BF_OK;
@@ -725,6 +737,7 @@ int bf_set_weights_async(bf_plan_t p, const double* pos, const double* dir, cons
     if (e != hipSuccess) return from_hip(e);
     const int st = generate_weights(p, pos, dir, freq, p->w_alt, s);
     if (st != BF_OK) return st;
+    p->w_max_alt = 1.0;
     e = hipEventRecord(p->w_ready, s);
     if (e != hipSuccess) return from_hip(e);
     p->refresh_pending = true;
@@ -836,8 +849,11 @@ int bf_set_weights_raw(bf_plan_t p, const double* w, void* stream) {
   try {
     if (!p || !w) return BF_ERR_INVALID_ARG;
     const size_t n = (size_t)p->C * p->B * p->N * 2;
-    for (size_t i = 0; i < n; ++i)
+    double most = 0.0;
+    for (size_t i = 0; i < n; ++i) {
       if (!std::isfinite(w[i])) return BF_ERR_INVALID_ARG;
+      most = std::max(most, std::fabs(w[i]));
+    }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     double* dw = nullptr;
     hipError_t e = hipMalloc(&dw, n * sizeof(double));
@@ -849,6 +865,7 @@ int bf_set_weights_raw(bf_plan_t p, const double* w, void* stream) {
     (void)hipFree(dw);
     if (e != hipSuccess) return from_hip(e);
     if (e2 != hipSuccess) return from_hip(e2);
+    p->w_max = most;
     p->refresh_pending = false;  // superseded
     p->weights_set = true;
     return BF_OK;

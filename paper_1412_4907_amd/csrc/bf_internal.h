@@ -34,6 +34,8 @@ struct Prob {
                       // ranges of one time range run back to back and share its
                       // voltages through L2
   float out_scale;    // complex output: factor applied to B before FP16 rounding
+  float w_scale;      // FP32, complex output: power of two applied to the weights as
+                      // they are split (out_scale holds its inverse)
 };
 
 struct Launch {
