@@ -123,7 +123,9 @@ Prob make_prob(const bf_plan_s* p, const Tile& form, int32_t sgw, const int8_t* 
   q.SG = SG;
   q.sgw = sgw = bf::wave_sgw(*p, form, sgw);
   // the plan's beam tiles spread evenly over as few ranges as the form's
-  // width allows: 9 tiles at width 4 run as 3 + 3 + 3 (measured in choose_tile)
+  // width allows: 9 tiles at width 4 run as 3 + 3 + 3, not 4 + 4 + 1 (144 beams, 128
+  // channels, 7680 samples, I = 16, FP16: N = 64 84 -> 75 us, N = 256 286 -> 259;
+  // FP32, N = 64 189 -> 160; 80 beams 10 % as well; 13 tiles and I = 1 within 1 %)
   const int32_t need = p->Bpad / 16;
   q.nbr = (need + form.nbt - 1) / form.nbt;
   q.bw = (need + q.nbr - 1) / q.nbr;

@@ -307,6 +307,15 @@ int64_t units_for(const Shape& s, Tile t, int32_t sgw) {
 // nothing: 1.4 times); and its HBM bytes at the CU's share of the bandwidth (8
 // bytes a cycle; the voltages are fetched once for all beam ranges of a
 // channel).
+// The constants: 16 cycles per MFMA, 40 VALU instructions per row tile and half
+// chunk of conversion and 32 of detection per beam and row tile are counted from
+// the kernels; the others were set by hand.  Over 89 drawn single runs (N 2 to 512,
+// B 1 to 1000, every precision, input and output), each timed under every form and
+// unit length, the choice takes 1.07 of the best one's time on average (median
+// 1.02, nine in ten below 1.18).  That mean is flat in the hand-set ones: staging 0
+// or 16000 cycles 1.064, 1.069; 4 or 16 LDS bytes a cycle 1.069, 1.061; VALU weight
+// 1 or 2.4 instead of 1.6 1.072, 1.056; the lone wave's 1.4 as 1 or 2 1.079, 1.065,
+// and without its rule 1.085; 4 or 16 HBM bytes a cycle 1.089, 1.067.
 double unit_cycles(const Shape& s, Tile f, int32_t v, int wg) {
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
@@ -332,7 +341,8 @@ double unit_cycles(const Shape& s, Tile f, int32_t v, int wg) {
 
 // Cycles of one launch: units run over the device's workgroup slots in whole
 // rounds, or, over many rounds, until a quarter of a unit after the last slot
-// frees.  Eight waves cost 5% more at a tie.
+// frees.  Eight waves cost 5% more at a tie.  (Over the same runs: half a unit or
+// none instead of the quarter 1.066, 1.069; no 5% or 15% 1.062, 1.075.)
 static double form_cycles(const Shape& s, const Tile& f, int32_t v) {
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
@@ -361,7 +371,8 @@ static double form_cycles(const Shape& s, const Tile& f, int32_t v) {
 // (N = 32, 512 beams, I = 1: 218 us at 16, 222 at 32, 245 at 8; 16 complex
 // beams: 762 at 4, 786 at 8, 816 at 32).  The general form at one chunk, which
 // runs where rows are over 100 MB apart: 64 (N = 32, 64 beams, 35.6 M samples: 2.67
-// to 2.86 ms at 16, 2.64 at 32 and 64, 2.78 at 256).
+// to 2.86 ms at 16, 2.64 at 32 and 64, 2.78 at 256).  Over the runs of unit_cycles
+// the mean is 1.066 with these caps, 1.068 with 64 for all.
 static int32_t best_sgw(const Shape& s, const Tile& f, int32_t base, double* cycles) {
   int32_t G, QI, SG;
   schedule(s.I, s.T, &G, &QI, &SG);
