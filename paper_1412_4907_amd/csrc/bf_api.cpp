@@ -851,11 +851,11 @@ int bf_set_weights_raw(bf_plan_t p, const double* w, void* stream) {
   try {
     if (!p || !w) return BF_ERR_INVALID_ARG;
     const size_t n = (size_t)p->C * p->B * p->N * 2;
-    double most = 0.0;
-    for (size_t i = 0; i < n; ++i) {
+    for (size_t i = 0; i < n; ++i)
       if (!std::isfinite(w[i])) return BF_ERR_INVALID_ARG;
-      most = std::max(most, std::fabs(w[i]));
-    }
+    double most = 1.0;
+    if (p->cx && p->prec == BF_FP32)  // read in make_prob
+      for (size_t i = 0; i < n; ++i) most = std::max(most, std::fabs(w[i]));
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     double* dw = nullptr;
     hipError_t e = hipMalloc(&dw, n * sizeof(double));
