@@ -529,9 +529,9 @@ bool wide_sets(const BatchSet* sets, int n, bool* wide) {
     if (v >= 0 && s.Bpad > 32 && split_lds_bytes(s.prec, s.Kpad, 4) > 80 * 1024)
       cramped += units_for(s, kWideTiles[v], sgw);
   }
-  const bool short_steps = sets[0].s->mode == kModeI1 || sets[0].s->mode == kModeGen4;
-  if (all && (want >= 2 * (int64_t)n_cu || (sets[0].s->prec != BF_FP32 && short_steps &&
-                                            4 * cramped >= 3 * (int64_t)n_cu))) {
+  const bool cramp = sets[0].s->prec != BF_FP32 && sets[0].s->mode == kModeGen4 &&
+                     4 * cramped >= 3 * (int64_t)n_cu;
+  if (all && (want >= 2 * (int64_t)n_cu || cramp)) {
     for (int i = 0; i < n; ++i) wide[i] = true;
     return true;
   }

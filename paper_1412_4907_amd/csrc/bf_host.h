@@ -128,10 +128,11 @@ struct BatchSet {
 // One launch of the eight-wave form takes them all where every set has more than
 // two chunks of K and either the sets whose own tile it is have two units per CU
 // (FP32, N 256 / 256 / 304, 64, 16 and 8 channels, I = 16: 834 -> 403 us), or, in
-// 16 bits at I == 1 or I % 4 == 0, the sets for whose four beam tiles two
-// four-wave workgroups do not fit a CU make up 3/4 unit per CU there (N 200 and
-// 256, 32 channels, FP16: I = 16 143 -> 109 us, I = 64 151 -> 135, I = 1 185 both;
-// with 64 units of N = 256 the four-wave launch stays: 41 against 59).
+// 16 bits at I % 4 == 0, the sets for whose four beam tiles two four-wave
+// workgroups do not fit a CU make up 3/4 unit per CU there (N 200 and 256, 32
+// channels, FP16: I = 16 143 -> 109 us, I = 64 151 -> 135, but 178 -> 186 at I = 1
+// and 138 -> 145 at I = 2; with 64 units of N = 256 the four-wave launch stays: 41
+// against 59).
 // Else two launches, where both fill the device several times: each drains on
 // its own (four sets of 10 to 112 channels: 308 us split, 110 together).
 bool wide_sets(const BatchSet* sets, int n, bool* wide);

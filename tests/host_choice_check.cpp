@@ -102,6 +102,8 @@ static int check_wide_batches() {
     }
   const Set pair[] = {{200, 32, 300, 240, false}, {256, 32, 100, 240, false}};
   CHECK(wide_of(pair, 2, 16, BF_FP16) == 2);
+  const Set pair1[] = {{200, 32, 300, 3840, false}, {256, 32, 100, 3840, false}};
+  CHECK(wide_of(pair1, 2, 1, BF_FP16) == 0);
   const Set one[] = {{256, 64, 64, 120, false}};
   CHECK(wide_of(one, 1, 16, BF_FP16) == 0);
   const Set tiny[] = {{256, 8, 64, 1920, false}};
