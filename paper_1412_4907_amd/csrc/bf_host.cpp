@@ -420,11 +420,14 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
     *out_sgw = v;
   };
   if (s.prec != BF_FP32 && s.vec16 && s.mode != kModeGen && need > 1 &&
-      lds_bytes(s.prec, s.Kpad, 2) <= kLdsMax && split_lds_bytes(s.prec, s.Kpad, 2) > kLdsMax) {
+      lds_bytes(s.prec, s.Kpad, 2) <= kLdsMax && split_lds_bytes(s.prec, s.Kpad, 2) > kLdsMax &&
+      units_for(s, Tile{4, 2, 2, 0}, base_sgw(s, 4)) >= s.n_cu) {
     // N = 552 .. 608: two beam tiles' weights fit LDS only in the general form's
     // rows, which have no padding per chunk (N = 600 x 27 channels, 256 beams, 7680
     // samples, FP16, against the streamed form's one tile: I = 64 697 -> 465 us,
-    // I = 16 653 -> 446, I = 1 147 -> 132; I = 5, with dummy rows, 602 -> 671)
+    // I = 16 653 -> 446, I = 1 147 -> 132; I = 5, with dummy rows, 602 -> 671).  With
+    // fewer units than CUs one tile's twice as many finish first (N = 560 x 8
+    // channels, 395 beams, 1344 4-bit samples, I = 64: 197 -> 136)
     *out = Tile{4, 2, 2, 0};
     *out_sgw = choose_sgw(s, *out);
     return;

@@ -45,6 +45,7 @@ static int check_large_arrays() {
       }
   for (int N : {544, 552, 608, 616})
     CHECK(chosen(N, 27, 256, 7680, 5, BF_FP16).kres < -1);  // dummy rows: streamed
+  CHECK(chosen(560, 8, 395, 1344, 64, BF_FP16).kres < -1);  // 104 units for 256 CUs
   CHECK(chosen(544, 27, 256, 7680, 64, BF_FP16).kres < -1);  // two streamed tiles fit
   CHECK(chosen(544, 27, 256, 7680, 64, BF_FP16).nbt == 2);
   CHECK(chosen(616, 27, 256, 7680, 64, BF_FP16).kres < -1);
