@@ -460,11 +460,16 @@ void choose_tile(const Shape& s, Tile* out, int32_t* out_sgw) {
   }
   if (found) return;
   Tile t{4, 1, 1, 0};
-  if (lds_bytes(s.prec, s.Kpad, 1) > (s.vec16 ? kLdsMax : (size_t)80 * 1024)) {
+  const size_t lds1 = lds_bytes(s.prec, s.Kpad, 1);
+  if (lds1 > kLdsMax ||
+      (!s.vec16 && lds1 > 80 * 1024 && units_for(s, t, base_sgw(s, t.mt)) > s.n_cu)) {
     // one beam tile's weights do not fit LDS; or they leave one workgroup per
     // CU, whose four waves wait for each byte of a byte-load row (N = 1121 x 14
     // channels, 256 beams, FP16: I = 5 12.3 -> 4.6 ms, I = 64 9.6 -> 5.8, I = 1
-    // 1.86 -> 0.89; 16 beams, I = 5: 1.13 -> 0.85; FP32, N = 601: 6.4 -> 2.5)
+    // 1.86 -> 0.89; 16 beams, I = 5: 1.13 -> 0.85; FP32, N = 601: 6.4 -> 2.5).
+    // With no more units than CUs there is one per CU in either form, and LDS is
+    // the faster (N = 1121 x 2 channels, 49984 samples, I = 64: 16 beams 4.91
+    // against 4.67, 35 beams 5.15 against 4.66; FP32, N = 601: 3.02 against 2.79)
     t = Tile{4, 2, 2, -1};
   } else {
     int nbt = s.prec == BF_FP32 ? 8 : 4;

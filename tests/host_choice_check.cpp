@@ -51,10 +51,16 @@ static int check_large_arrays() {
   CHECK(chosen(616, 27, 256, 7680, 64, BF_FP16).kres < -1);
   for (int I : {1, 5, 64}) {
     CHECK(chosen(1121, 14, 256, 7680, I, BF_FP16).kres == -1);
-    CHECK(chosen(1121, 14, 16, 7680, I, BF_BF16).kres == -1);
+    CHECK(chosen(1121, 14, 16, 7680, I, BF_BF16).kres == (I == 64 ? 0 : -1));  // 112 units
     CHECK(chosen(601, 14, 256, 7680, I, BF_FP32).kres == -1);
     CHECK(chosen(1120, 14, 256, 7680, I, BF_FP16).kres == 0);  // 16-byte rows keep LDS
   }
+  // no more units than CUs: LDS
+  CHECK(chosen(1121, 2, 16, 49984, 64, BF_FP16).kres == 0);
+  CHECK(chosen(1121, 2, 16, 50000, 16, BF_BF16).kres == 0);
+  CHECK(chosen(1121, 2, 35, 50000, 16, BF_BF16).kres == -1);
+  CHECK(chosen(601, 2, 35, 49984, 64, BF_FP32).kres == 0);
+  CHECK(chosen(601, 2, 160, 49984, 64, BF_FP32).kres == -1);
   return 0;
 }
 

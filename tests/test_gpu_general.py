@@ -141,7 +141,7 @@ def test_large_rows_by_default(gpu, N, prec):
     """Arrays whose default is the general form for its weights' size: byte-load
     rows with the weights in device memory, and two beam tiles in LDS."""
     print(f"general large N={N} {prec}", flush=True)
-    C, B, T, I = (2, 40, 96, 16) if N % 8 else (64, 128, 96, 16)  # the latter: 256 units
+    C, B, T, I = 64, 128, 96, 16  # at least one unit per CU in each form
     geo = _geometry(N, C, B, N)
     x = np.random.default_rng(N).integers(-128, 128, (C, T, N, 2)).astype(np.int8)
     with bf.Plan(N, C, B, T, I, precision=prec) as plan:
