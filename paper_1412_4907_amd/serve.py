@@ -21,7 +21,8 @@ builds those ideas on one MI355X:
   k mod slots, so a block's output stays intact while the later blocks that
   can be in flight run); integration state never leaves HBM;
 * the per-block work -- one persistent beamform launch over every active
-  request -- reads its set table (which requests,
+  request, behind a small kernel that clears its queue counters -- reads its
+  set table (which requests,
   which ring slot, which output buffers) from device memory, so it is
   captured once as a hipGraph and replayed for every block; before each
   replay a one-workgroup kernel stores that block's table;
